@@ -61,7 +61,7 @@ extern "C" {
 
 /* kernel variants of the step loop (fd3d_set_kernel) */
 #define FD3D_KERNEL_CELL 0 /* one thread per cell, neighbours from global memory */
-#define FD3D_KERNEL_TILE 1 /* LDS-staged x/y halo planes + register z sweep (default) */
+#define FD3D_KERNEL_TILE 1 /* LDS-staged x/y halo planes + register z sweep */
 #define FD3D_KERNEL_FUSED 2 /* velocity and stress of a step in one z sweep over a double-buffered
                                state; tiles 64x4 and 64x8 (FP32), 64x4 (FP64) */
 
@@ -348,9 +348,11 @@ typedef struct fd3d_kernel {
     int zchunk;   /* z planes swept by one workgroup, >= 4 */
 } fd3d_kernel;
 
-/* Default at create: FD3D_KERNEL_TILE with 256x4 tiles (FP32, nx >= 256), 128x4
- * (nx >= 128) or 64x8, and 64-plane sweeps (nz >= 128) or 32.  FD3D_EINVAL for an
- * unsupported shape.  The fused variant keeps two copies of the state and swaps them
+/* Default at create, until fd3d_set_kernel or fd3d_autotune selects one: each operation on
+ * the context (forward, gradient, Born) picks the cell or the tile kernels by the size of its
+ * working set (cell while that stays in the Infinity Cache), with the tile shape and sweep
+ * depth that fill the chip in one round; fd3d_get_kernel returns what the forward runs.
+ * FD3D_EINVAL for an unsupported shape.  The fused variant keeps two copies of the state and swaps them
  * every step; the state accessors always address the current copy, and the gradient's
  * segment recompute and adjoint passes use the tile kernels of the same tile shape. */
 int fd3d_set_kernel(fd3d_ctx *ctx, const fd3d_kernel *k);

@@ -23,6 +23,8 @@ struct BatchGroup {
     int s0, ns, tiles, recs, wgs;
     int tx, ty, tx2, ty2;
     int vac;  // some shot of the group has a vacuum surface
+    long cols;  // columns of tiles over all shots of the launch
+    int rows, rtiles;  // row kernels, and their blocks
     int ntp;  // cache policy of the group's forward passes (see group_streams)
 };
 
@@ -35,6 +37,7 @@ struct fd3d_batch {
     size_t off_fwd, off_rec;
     int tile_x, tile_y, wgs_req;
     int tile2_x, tile2_y;  // optional second tile shape (same workgroup size), 0: none
+    bool tiles_set;        // the caller or the tuner selected the batch's tile shapes
     size_t group_bytes;    // 0: lockstep; otherwise the cache-blocked group budget
     std::vector<BatchGroup> groups;
     std::vector<int> order;  // shot at each position of the descriptor arrays
@@ -164,8 +167,69 @@ TileMap shot_tiles(const BatchGroup &b, const fd3d_ctx *c, int &alt)
     tm.ntx = (c->n[0] + tx - 1) / tx;
     tm.nty = (c->n[1] + ty - 1) / ty;
     tm.zc = c->zchunk;
-    tm.nzc = (c->n[2] + c->zchunk - 1) / c->zchunk;
+    // no depth selected: the launch's shots share one round
+    if ((c->auto_kernel || c->variant == FD3D_KERNEL_CELL) && b.cols > 0) {
+        tm.zc = sweep_depth(c->n[2], b.cols, tile_slots(c->tsize, tx * ty));
+        while (tm.zc > 4 && !window_ok(c, tm.zc)) tm.zc = std::max(4, tm.zc / 2);
+    }
+    tm.nzc = (c->n[2] + tm.zc - 1) / tm.zc;
     return tm;
+}
+
+// Columns of tiles over ns shots of a launch.
+template <typename C> long tile_columns(const BatchGroup &g, int ns, C &&shot)
+{
+    long cols = 0;
+    for (int q = 0; q < ns; ++q) {
+        int alt = 0;
+        const TileMap tm = shot_tiles(g, shot(q), alt);
+        cols += (long)tm.ntx * tm.nty;
+    }
+    return cols;
+}
+
+// Whether the launches over these shots run the row kernels: when no shot has a tile or fused
+// kernel selected and the arrays of all of them (`arrays` per shot) together stay in the
+// Infinity Cache (kernels_of).  In lockstep, us per step, rows / tile sweeps: six shots of 40 x 50
+// x 60 30.3 / 78.3 (31.3 with the depth of one round), three of 40^3 13.2, four of 96 x 80 x 72
+// (106 MB) 56.4 / 81.8.
+bool batch_rows(const fd3d_ctx *const *ctx, int ns, int arrays)
+{
+    double bytes = 0.0;
+    if (ns == 1 && arrays == kForwardArrays) return kernels_of(ctx[0], arrays) == Kern::rows;
+    for (int q = 0; q < ns; ++q) {
+        const fd3d_ctx *c = ctx[q];
+        if (!rows_ok(c) || (!c->auto_kernel && c->variant != FD3D_KERNEL_CELL)) return false;
+        bytes += (double)arrays * c->n[0] * c->n[1] * c->n[2] * c->tsize;
+    }
+    return bytes <= (ctx[0]->tsize == 8 ? kRowBytes64 : kRowBytes32);
+}
+
+// One pass over a group with the row kernels.
+template <typename T, bool FS>
+void launch_rows_multi(const BatchGroup &gr, const ShotFwd<T> *d, int n, int pass, hipStream_t st, const ShotRec<T> *r, int nt)
+{
+    const int S = gr.ns, W = gr.rtiles, g = (W + 7) / 8 * 8;
+    const RecMulti<T> rec{r, S, (r && pass == kPassStress) ? gr.recs : 0, nt, g};
+    const int gs = g + rec_blocks(rec, 256);
+    if constexpr (!FS) {
+        if (gr.vac && pass == kPassVel) {
+            vel_row_multi<T, false, kFwd, true><<<g, 256, 0, st>>>(d, S, W, n);
+            return;
+        }
+        if (gr.vac && pass == kPassStress) {
+            stress_row_multi<T, false, kFwd, true><<<gs, 256, 0, st>>>(d, S, W, n, rec);
+            return;
+        }
+    }
+    switch (pass) {
+    case kPassVel: vel_row_multi<T, FS, kFwd, false><<<g, 256, 0, st>>>(d, S, W, n); break;
+    case kPassStress: stress_row_multi<T, FS, kFwd, false><<<gs, 256, 0, st>>>(d, S, W, n, rec); break;
+    case kPassVelSave: vel_row_multi<T, false, kFwdSave, false><<<g, 256, 0, st>>>(d, S, W, n); break;
+    case kPassStressM: stress_row_multi<T, false, kAdjM, false><<<g, 256, 0, st>>>(d, S, W, n, rec); break;
+    case kPassVelA: vel_row_multi<T, false, kAdjA, false><<<g, 256, 0, st>>>(d, S, W, n); break;
+    default: stress_row_multi<T, false, kAdjB, false><<<g, 256, 0, st>>>(d, S, W, n, rec); break;
+    }
 }
 
 // One pass over the shots of group gr; d points at the group's first descriptor.  A
@@ -223,6 +287,10 @@ template <typename T, bool FS>
 int multi_pass(const BatchGroup &b, const ShotFwd<T> *d, int n, int pass, hipStream_t st, const ShotRec<T> *r = nullptr,
                int nt = 0)
 {
+    if (b.rows) {
+        launch_rows_multi<T, FS>(b, d, n, pass, st, r, nt);
+        return FD3D_OK;
+    }
     return with_batch_tiles<T>(b, [&](auto tx, auto ty, auto tx2, auto ty2) {
         return launch_multi<T, decltype(tx)::value, decltype(ty)::value, decltype(tx2)::value, decltype(ty2)::value,
                             FS>(b, d, n, pass, st, r, nt);
@@ -274,8 +342,10 @@ void make_groups(fd3d_batch *b)
     b->groups.clear();
     b->order.resize(b->nshot);
     for (int s = 0; s < b->nshot; ++s) b->order[s] = s;
-    const BatchGroup all = whole_batch(b);
+    BatchGroup all = whole_batch(b);
     if (b->group_bytes == 0) {
+        all.cols = tile_columns(all, b->nshot, [&](int q) { return b->ctx[q]; });
+        all.rows = !b->tiles_set && batch_rows(b->ctx.data(), b->nshot, kForwardArrays);
         b->groups.push_back(all);
         return;
     }
@@ -293,16 +363,18 @@ void make_groups(fd3d_batch *b)
         std::vector<const fd3d_ctx *> members;
         for (int q = s; q < e; ++q) members.push_back(ctx_at(q));
         g.ntp = group_streams(members.data(), g.ns);
+        g.rows = batch_rows(members.data(), g.ns, kForwardArrays);
         const fd3d_ctx *c0 = ctx_at(s);
-        bool same = c0->variant == FD3D_KERNEL_TILE;
+        auto tiled = [](const fd3d_ctx *c) { return c->variant == FD3D_KERNEL_TILE || c->auto_kernel; };
+        bool same = tiled(c0);
         for (int q = s + 1; q < e && same; ++q)
-            same = ctx_at(q)->variant == FD3D_KERNEL_TILE && ctx_at(q)->tile_x == c0->tile_x &&
-                   ctx_at(q)->tile_y == c0->tile_y;
+            same = tiled(ctx_at(q)) && ctx_at(q)->tile_x == c0->tile_x && ctx_at(q)->tile_y == c0->tile_y;
         if (same && tile_supported(b->tsize, c0->tile_x, c0->tile_y)) {
             g.tx = c0->tile_x;
             g.ty = c0->tile_y;
             g.tx2 = g.ty2 = 0;
         }
+        g.cols = tile_columns(g, g.ns, [&](int q) { return ctx_at(s + q); });
         b->groups.push_back(g);
         s = e;
     }
@@ -316,12 +388,12 @@ int batch_forward_impl(fd3d_batch *b, const fd3d_source *srcs, const int *nrec, 
     std::vector<ShotRec<T>> rr(b->nshot);
     make_groups(b);
     size_t gi = 0;
-    int tiles = 0, recs = 0;
+    int tiles = 0, recs = 0, rtiles = 0;
     for (int p = 0; p < b->nshot; ++p) {  // position p of the schedule order holds shot s
         const int s = b->order[p];
         fd3d_ctx *c = b->ctx[s];
         BatchGroup &grp = b->groups[gi];
-        if (p == grp.s0) tiles = recs = grp.vac = 0;  // work items and receivers count from the group's first
+        if (p == grp.s0) tiles = rtiles = recs = grp.vac = 0;  // work items and receivers count from the group's first
         if (c->opts.vacuum_top > 0) grp.vac = 1;
         if (!window_ok(c, c->zchunk))
             return fail(FD3D_EINVAL, "shot " + std::to_string(s) + ": zchunk too large for a tile sweep");
@@ -337,6 +409,9 @@ int batch_forward_impl(fd3d_batch *b, const fd3d_source *srcs, const int *nrec, 
         fw[p].tm = tm;
         fw[p].base = tiles;
         tiles += tm.ntx * tm.nty * tm.nzc;
+        fw[p].rm = row_map(c, true);
+        fw[p].rbase = rtiles;
+        rtiles += fw[p].rm.ns * fw[p].rm.tiles() * fw[p].rm.np;
         for (int q = 0; q < 3; ++q) rr[p].v[q] = fw[p].G.f[VX + q];
         rr[p].taps = (const RecTap<T> *)(c->ws + c->L.rec);
         rr[p].traces = nr ? (T *)traces[s] : nullptr;
@@ -345,6 +420,7 @@ int batch_forward_impl(fd3d_batch *b, const fd3d_source *srcs, const int *nrec, 
         recs += 3 * nr;
         if (p == grp.s0 + grp.ns - 1) {
             grp.tiles = tiles;
+            grp.rtiles = rtiles;
             grp.recs = recs;
             ++gi;
         }
@@ -374,7 +450,7 @@ int batch_forward_impl(fd3d_batch *b, const fd3d_source *srcs, const int *nrec, 
         wgs = std::min(wgs, ((g.tiles + 7) / 8) * 8);
         g.wgs = std::max(8, (wgs + 7) / 8 * 8);
         for (long v : {(long)g.s0, (long)g.ns, (long)g.tiles, (long)g.recs, (long)g.wgs, (long)g.tx, (long)g.ty,
-                       (long)g.tx2, (long)g.ty2, (long)g.vac})
+                       (long)g.tx2, (long)g.ty2, (long)g.vac, (long)g.rows, (long)g.rtiles})
             mix(v);
     }
     if (!use_graph) return batch_sequence<T>(b, flags, st);
@@ -465,9 +541,10 @@ int batch_gradient_impl(fd3d_batch *b, const fd3d_source *srcs, const int *nrec,
     std::vector<ShotRec<T>> rr(S);
     std::vector<ShotInject<T>> ij(S);
     std::vector<AdjGrid<T>> ag(S);
-    int tiles = 0, recs = 0, ncol = 0;
+    int tiles = 0, rtiles = 0, recs = 0, ncol = 0;
     int cbase[kMaxBatchColors] = {0, 0, 0, 0};
     BatchGroup all = whole_batch(b);  // every shot in each launch (lockstep)
+    all.cols = tile_columns(all, S, [&](int q) { return b->ctx[q]; });
     for (int s = 0; s < S; ++s) {
         fd3d_ctx *c = b->ctx[s];
         const std::string tag = "shot " + std::to_string(s) + ": ";
@@ -493,6 +570,9 @@ int batch_gradient_impl(fd3d_batch *b, const fd3d_source *srcs, const int *nrec,
         fw[s].tm = tm;
         fw[s].base = tiles;
         tiles += tm.ntx * tm.nty * tm.nzc;
+        fw[s].rm = row_map(c, true);
+        fw[s].rbase = rtiles;
+        rtiles += fw[s].rm.ns * fw[s].rm.tiles() * fw[s].rm.np;
         for (int q = 0; q < 3; ++q) rr[s].v[q] = fw[s].G.f[VX + q];
         rr[s].taps = (const RecTap<T> *)(c->ws + c->L.rec);
         rr[s].traces = (T *)traces[s];
@@ -579,9 +659,13 @@ int batch_gradient_impl(fd3d_batch *b, const fd3d_source *srcs, const int *nrec,
     int wgs = b->wgs_req > 0 ? b->wgs_req : cus * occ;
     all.wgs = std::max(8, (std::min(wgs, ((tiles + 7) / 8) * 8) + 7) / 8 * 8);
     all.tiles = tiles;
+    all.rtiles = rtiles;
     all.recs = recs;
+    BatchGroup fwd = all;
+    fwd.rows = !b->tiles_set && batch_rows(b->ctx.data(), S, kForwardArrays);
+    all.rows = !b->tiles_set && batch_rows(b->ctx.data(), S, kAdjointArrays);
 
-    const bool merged = all.tx2 == 0;  // stress-M (one tile shape)
+    const bool merged = all.rows || all.tx2 == 0;  // stress-M (row kernels, or one tile shape)
     // forward with checkpoints
     auto desc = [&](size_t off) { return (const ShotFwd<T> *)(bws + off); };
     const ShotRec<T> *rdesc = (const ShotRec<T> *)(b->ws + b->off_rec);
@@ -589,12 +673,12 @@ int batch_gradient_impl(fd3d_batch *b, const fd3d_source *srcs, const int *nrec,
     if (!(flags & FD3D_KEEP_STATE))
         for (fd3d_ctx *c : b->ctx) zero_fields<T>(c, st);
     auto pass = [&](const ShotFwd<T> *d, int n, int p, const ShotRec<T> *r = nullptr) {
-        multi_pass<T, false>(all, d, n, p, st, r, b->nt);
+        multi_pass<T, false>(r ? fwd : all, d, n, p, st, r, b->nt);
     };
     for (int n = 0; n < b->nt; ++n) {
         if (n % k == 0)
             copy_multi<T><<<cgrid, 256, 0, st>>>((const CopyDesc<T> *)(bws + BL.save_copy + (n / k) * BL.copy_bytes));
-        pass(desc(BL.fwd0), n, kPassVel);
+        multi_pass<T, false>(fwd, desc(BL.fwd0), n, kPassVel, st);
         pass(desc(BL.fwd0), n, kPassStress, rdesc);  // also samples the receivers
     }
     // residuals and misfits, zeroed adjoint state, accumulators and segment slots
@@ -703,6 +787,7 @@ int fd3d_batch_create(fd3d_batch **out, int nshot, fd3d_ctx *const *ctxs, void *
     else if (minx >= 128) { b->tile_x = 128; b->tile_y = 4; }
     else { b->tile_x = 64; b->tile_y = 8; }
     b->wgs_req = 0;
+    b->tiles_set = false;
     b->tile2_x = b->tile2_y = 0;
     b->staged_pending = false;
     b->graph_valid = false;
@@ -739,6 +824,7 @@ int fd3d_batch_set_tiles(fd3d_batch *b, int tile_x, int tile_y, int tile2_x, int
     b->tile2_x = tile2_x;
     b->tile2_y = tile2_y;
     b->wgs_req = workgroups;
+    b->tiles_set = true;
     return FD3D_OK;
 }
 
@@ -762,6 +848,8 @@ int fd3d_batch_autotune(fd3d_batch *b, int steps, int best[6], double *best_ms, 
     static const int budgets[] = {96, 128, 192, 256, 384};
     const int nt_save = b->nt;
     const size_t keep_group = b->group_bytes;
+    const bool keep_set = b->tiles_set;
+    bool win_set = keep_set;
     const int keep[5] = {b->tile_x, b->tile_y, b->tile2_x, b->tile2_y, b->wgs_req};
     int win[5] = {keep[0], keep[1], keep[2], keep[3], keep[4]};
     int win_mib = 0;
@@ -791,7 +879,16 @@ int fd3d_batch_autotune(fd3d_batch *b, int steps, int best[6], double *best_ms, 
         ms = 0.0f;
         (void)hipEventElapsedTime(&ms, e0, e1);
     };
+    b->tiles_set = false;
+    if (batch_rows(b->ctx.data(), b->nshot, kForwardArrays)) {  // the row kernels in lockstep
+        float ms = 0.0f;
+        time_it(ms);
+        win_ms = ms;
+        win_set = false;
+    }
+    b->tiles_set = true;
     for (const auto &sh : shapes) {
+        if (rc) break;
         if (!tile_supported(b->tsize, sh[0], sh[1])) continue;
         if (sh[2] && !pair_supported(b->tsize, sh[0], sh[1], sh[2], sh[3])) continue;
         // persistent grid (CUs x occupancy) or one workgroup per tile
@@ -803,7 +900,8 @@ int fd3d_batch_autotune(fd3d_batch *b, int steps, int best[6], double *best_ms, 
             b->wgs_req = 0;
             if (mode == 1) {
                 long tiles = 0;
-                const BatchGroup all = whole_batch(b);
+                BatchGroup all = whole_batch(b);
+                all.cols = tile_columns(all, b->nshot, [&](int q) { return b->ctx[q]; });
                 for (const fd3d_ctx *c : b->ctx) {
                     int alt = 0;
                     const TileMap tm = shot_tiles(all, c, alt);
@@ -816,6 +914,7 @@ int fd3d_batch_autotune(fd3d_batch *b, int steps, int best[6], double *best_ms, 
             if (rc) break;
             if (ms < win_ms) {
                 win_ms = ms;
+                win_set = true;
                 win[0] = b->tile_x;
                 win[1] = b->tile_y;
                 win[2] = b->tile2_x;
@@ -852,6 +951,7 @@ int fd3d_batch_autotune(fd3d_batch *b, int steps, int best[6], double *best_ms, 
     b->tile2_x = use[2];
     b->tile2_y = use[3];
     b->wgs_req = use[4];
+    b->tiles_set = rc ? keep_set : win_set;
     b->group_bytes = rc ? keep_group : (size_t)win_mib << 20;
     if (rc) return rc;
     for (fd3d_ctx *c : b->ctx) zero_fields_any(c, st);

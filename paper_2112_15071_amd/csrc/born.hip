@@ -52,14 +52,15 @@ int born_impl(fd3d_ctx *c, fd3d_ctx *dc, const fd3d_source *src, const void *dla
         if (vel) born_vel_source<T><<<grd, blk, 0, st>>>(G, dv, (const T *)drho, inj, n);
         else born_stress_source<T><<<grd, blk, 0, st>>>(G, ds, (const T *)dlam, (const T *)dmu);
     };
-    const bool tiled = c->variant == FD3D_KERNEL_TILE;
+    const Kern kern = kernels_of(c, kBornArrays);
     const TileMap tm = tile_map(c);
     const int nwg = tm.ntx * tm.nty * tm.nzc;
     const RecJob<T> recd = rec_job<T>(D.f[VX], D.f[VY], D.f[VZ], dtaps, nrec, c->nt, (T *)dtraces);
     const RecJob<T> recg = rec_job<T>(G.f[VX], G.f[VY], G.f[VZ], taps, traces ? nrec : 0, c->nt, (T *)traces);
-    if (tiled) {
+    if (kern != Kern::cells) {
         // the background and the perturbation in one velocity sweep and one stress sweep
-        // (the Born modes of the tile bodies); the stress sweep samples both receiver sets
+        // (the Born modes of the tile and row bodies); the stress sweep samples both
+        // receiver sets
         TileIO<T> iov, ios;
         std::memset(&iov, 0, sizeof iov);
         std::memset(&ios, 0, sizeof ios);
@@ -75,7 +76,14 @@ int born_impl(fd3d_ctx *c, fd3d_ctx *dc, const fd3d_source *src, const void *dla
         ios.acc[0] = (T *)dlam;
         ios.acc[1] = (T *)dmu;
         const bool ntp = sizeof(T) == 4 && stream_model(c);  // cache policy, as in launch_pass
+        const RowMap rm = row_map(c);
+        const dim3 gv = row_grid(rm), gs = row_grid(rm, recg.nq + recd.nq);
         for (int n = 0; n < c->nt; ++n) {
+            if (kern == Kern::rows) {
+                vel_row_io<T, kBornV><<<gv, 256, 0, st>>>(G, inj, n, rm, iov);
+                stress_row_io<T, kBornS><<<gs, 256, 0, st>>>(G, inj, n, rm, ios, recg, recd);
+                continue;
+            }
             with_tile<T>(c->tile_x, c->tile_y, [&](auto tx, auto ty) {
                 constexpr int TX = decltype(tx)::value, TY = decltype(ty)::value, NT = TX * TY;
                 const int nb = nwg + (recg.nq + recd.nq + NT - 1) / NT;
@@ -93,12 +101,12 @@ int born_impl(fd3d_ctx *c, fd3d_ctx *dc, const fd3d_source *src, const void *dla
     }
     for (int n = 0; n < c->nt; ++n) {
         born_source(n, true);
-        launch_pass<T, false>(dc, D, dinj, n, kPassVel, st);
-        launch_pass<T, false>(c, G, inj, n, kPassVel, st);
+        launch_pass<T, false>(dc, kern, D, dinj, n, kPassVel, st);
+        launch_pass<T, false>(c, kern, G, inj, n, kPassVel, st);
         born_source(n, false);
         // the stress launches sample the perturbation's and the background's receivers
-        launch_pass<T, false>(dc, D, dinj, n, kPassStress, st, TileIO<T>{}, recd);
-        launch_pass<T, false>(c, G, inj, n, kPassStress, st, TileIO<T>{}, recg);
+        launch_pass<T, false>(dc, kern, D, dinj, n, kPassStress, st, recd);
+        launch_pass<T, false>(c, kern, G, inj, n, kPassStress, st, recg);
     }
     HIP_TRY(hipGetLastError());
     return FD3D_OK;

@@ -41,6 +41,29 @@ void launch_tiles(const Grid<T> &G, const Inject<T> &inj, int n, const TileMap &
     }
 }
 
+// One forward pass with the row kernels.
+template <typename T, bool FS>
+void launch_rows(const fd3d_ctx *c, const Grid<T> &G, const Inject<T> &inj, int n, int pass, hipStream_t st,
+                 const RecJob<T> &rec)
+{
+    const RowMap rm = row_map(c);
+    const dim3 g = row_grid(rm), gs = row_grid(rm, rec.nq);
+    if (G.save[VX] != nullptr && pass == kPassVel) pass = kPassVelSave;
+    if constexpr (!FS) {
+        if (G.ks > 0 && pass != kPassVelSave) {
+            if (pass == kPassVel) vel_row<T, false, kFwd, true><<<g, 256, 0, st>>>(G, inj, n, rm);
+            else stress_row<T, false, true><<<gs, 256, 0, st>>>(G, inj, n, rm, rec);
+            return;
+        }
+        if (pass == kPassVelSave) {  // the gradient's recompute (no free surface)
+            vel_row<T, false, kFwdSave, false><<<g, 256, 0, st>>>(G, inj, n, rm);
+            return;
+        }
+    }
+    if (pass == kPassVel) vel_row<T, FS, kFwd, false><<<g, 256, 0, st>>>(G, inj, n, rm);
+    else stress_row<T, FS, false><<<gs, 256, 0, st>>>(G, inj, n, rm, rec);
+}
+
 // Arguments of one fused step from the current state copy into the other one.
 template <typename T> FusedArgs<T> fused_args(const fd3d_ctx *c, const Inject<T> &inj, int n)
 {
@@ -120,10 +143,14 @@ void fused_step(fd3d_ctx *c, const Inject<T> &inj, int n, int nrec, const RecTap
 namespace fd3d {
 
 template <typename T, bool FS>
-void launch_pass(const fd3d_ctx *c, const Grid<T> &G, const Inject<T> &inj, int n, int pass, hipStream_t st,
-                 const TileIO<T> &, const RecJob<T> &rec)
+void launch_pass(const fd3d_ctx *c, Kern kern, const Grid<T> &G, const Inject<T> &inj, int n, int pass, hipStream_t st,
+                 const RecJob<T> &rec)
 {
-    if (c->variant == FD3D_KERNEL_CELL) {
+    if (kern == Kern::rows) {
+        launch_rows<T, FS>(c, G, inj, n, pass, st, rec);
+        return;
+    }
+    if (kern == Kern::cells) {
         const dim3 blk(64, 4, 1);
         const dim3 grd((G.nx + 63) / 64, (G.ny + 3) / 4, G.nz);
         if (pass == kPassVel) vel_cell<T, FS><<<grd, blk, 0, st>>>(G, inj, n);
@@ -143,14 +170,14 @@ void launch_pass(const fd3d_ctx *c, const Grid<T> &G, const Inject<T> &inj, int 
 }
 
 template <typename T, bool FS>
-void step(fd3d_ctx *c, const Grid<T> &G, const Inject<T> &inj, int n, int nrec, const RecTap<T> *taps, T *traces,
-          hipStream_t st, Timer &tm)
+void step(fd3d_ctx *c, Kern kern, const Grid<T> &G, const Inject<T> &inj, int n, int nrec, const RecTap<T> *taps,
+          T *traces, hipStream_t st, Timer &tm)
 {
     tm.begin(0);
-    launch_pass<T, FS>(c, G, inj, n, kPassVel, st);
+    launch_pass<T, FS>(c, kern, G, inj, n, kPassVel, st);
     tm.end();
     tm.begin(2);  // the stress launch also samples the receivers
-    launch_pass<T, FS>(c, G, inj, n, kPassStress, st, TileIO<T>{},
+    launch_pass<T, FS>(c, kern, G, inj, n, kPassStress, st,
                        rec_job<T>(G.f[VX], G.f[VY], G.f[VZ], taps, nrec, c->nt, traces));
     tm.end();
 }
@@ -171,6 +198,7 @@ int forward_impl(fd3d_ctx *c, const fd3d_source *src, int nrec, const double *re
     if (!(flags & FD3D_KEEP_STATE)) zero_fields<T>(c, st);
     const RecTap<T> *taps = (const RecTap<T> *)(c->ws + c->L.rec);
     const bool fused = c->variant == FD3D_KERNEL_FUSED;
+    const Kern kern = kernels_of(c, kForwardArrays);
     Timer tm{c, st};
     c->prof_used = 0;
     for (int n = 0; n < c->nt; ++n) {
@@ -183,8 +211,8 @@ int forward_impl(fd3d_ctx *c, const fd3d_source *src, int nrec, const double *re
         }
         if (fused && c->opts.free_surface) fused_step<T, true>(c, inj, n, nrec, taps, (T *)traces, st, tm);
         else if (fused) fused_step<T, false>(c, inj, n, nrec, taps, (T *)traces, st, tm);
-        else if (c->opts.free_surface) step<T, true>(c, G, inj, n, nrec, taps, (T *)traces, st, tm);
-        else step<T, false>(c, G, inj, n, nrec, taps, (T *)traces, st, tm);
+        else if (c->opts.free_surface) step<T, true>(c, kern, G, inj, n, nrec, taps, (T *)traces, st, tm);
+        else step<T, false>(c, kern, G, inj, n, nrec, taps, (T *)traces, st, tm);
     }
     HIP_TRY(hipGetLastError());
     const Grid<T> G = make_grid<T>(c);
@@ -202,10 +230,10 @@ int forward_impl(fd3d_ctx *c, const fd3d_source *src, int nrec, const double *re
 }
 
 #define FD3D_FORWARD_INSTANCES(T, FS)                                                                        \
-    template void launch_pass<T, FS>(const fd3d_ctx *, const Grid<T> &, const Inject<T> &, int, int, hipStream_t, \
-                                     const TileIO<T> &, const RecJob<T> &);                                  \
-    template void step<T, FS>(fd3d_ctx *, const Grid<T> &, const Inject<T> &, int, int, const RecTap<T> *, T *,  \
-                              hipStream_t, Timer &);
+    template void launch_pass<T, FS>(const fd3d_ctx *, Kern, const Grid<T> &, const Inject<T> &, int, int,      \
+                                     hipStream_t, const RecJob<T> &);                                         \
+    template void step<T, FS>(fd3d_ctx *, Kern, const Grid<T> &, const Inject<T> &, int, int, const RecTap<T> *, \
+                              T *, hipStream_t, Timer &);
 FD3D_FORWARD_INSTANCES(float, false)
 FD3D_FORWARD_INSTANCES(float, true)
 FD3D_FORWARD_INSTANCES(double, false)
@@ -248,6 +276,7 @@ int fd3d_set_kernel(fd3d_ctx *ctx, const fd3d_kernel *k)
     if (k->variant != FD3D_KERNEL_CELL && !window_ok(ctx, k->zchunk))
         return fail(FD3D_EINVAL, "zchunk too large: a sweep's window (zchunk + 8 planes, at most nz) must fit in 1 GiB");
     ctx->variant = k->variant;
+    ctx->auto_kernel = false;
     if (k->variant != FD3D_KERNEL_CELL) {
         ctx->tile_x = k->tile_x;
         ctx->tile_y = k->tile_y;
@@ -287,6 +316,8 @@ int fd3d_autotune(fd3d_ctx *ctx, int steps, fd3d_kernel *best, double *best_ms, 
     std::sort(chunks.begin(), chunks.end());
     const int nt_save = ctx->nt;
     const fd3d_kernel keep = {ctx->variant, ctx->tile_x, ctx->tile_y, ctx->zchunk};
+    const bool keep_auto = ctx->auto_kernel;
+    ctx->auto_kernel = false;
     fd3d_kernel win = keep;
     double win_ms = 1e300;
     hipEvent_t e0 = nullptr, e1 = nullptr;
@@ -340,6 +371,7 @@ int fd3d_autotune(fd3d_ctx *ctx, int steps, fd3d_kernel *best, double *best_ms, 
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
     const fd3d_kernel &use = rc ? keep : win;
+    ctx->auto_kernel = rc ? keep_auto : false;
     ctx->variant = use.variant;
     ctx->tile_x = use.tile_x;
     ctx->tile_y = use.tile_y;

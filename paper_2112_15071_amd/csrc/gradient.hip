@@ -9,11 +9,20 @@ namespace {
 
 // One adjoint pass of a tiled step (stress-A, stress-M, velocity-A, stress-B) on the
 // context's tile shape and cache policy (the streaming policy also covers the stored
-// velocities).
+// velocities), or with the row kernels (cell variant).
 template <typename T>
-void launch_adj_pass(const fd3d_ctx *c, const Grid<T> &G, const Inject<T> &inj, int n, int pass, hipStream_t st,
+void launch_adj_pass(const fd3d_ctx *c, Kern kern, const Grid<T> &G, const Inject<T> &inj, int n, int pass, hipStream_t st,
                      const TileIO<T> &io)
 {
+    if (kern == Kern::rows) {
+        const RowMap rm = row_map(c);
+        const dim3 g = row_grid(rm);
+        const RecJob<T> none{};
+        if (pass == kPassStressM) stress_row_io<T, kAdjM><<<g, 256, 0, st>>>(G, inj, n, rm, io, none, none);
+        else if (pass == kPassVelA) vel_row_io<T, kAdjA><<<g, 256, 0, st>>>(G, inj, n, rm, io);
+        else stress_row_io<T, kAdjB><<<g, 256, 0, st>>>(G, inj, n, rm, io, none, none);
+        return;
+    }
     const TileMap tm = tile_map(c);
     const int nwg = tm.ntx * tm.nty * tm.nzc;
     with_tile<T>(c->tile_x, c->tile_y, [&](auto tx, auto ty) {
@@ -57,7 +66,9 @@ int adjoint_impl(fd3d_ctx *c, const fd3d_source *src, int nrec, const double *re
     const RecTap<T> *taps = (const RecTap<T> *)(c->ws + c->L.rec);
     const int *colors = (const int *)(c->ws + c->L.colors);
     const dim3 blk(64, 4, 1), grd((G.nx + 63) / 64, (G.ny + 3) / 4, G.nz);
-    const bool tiled = c->variant != FD3D_KERNEL_CELL;  // the fused variant recomputes with tiles
+    // the row kernels run the tiled adjoint's passes; the fused variant recomputes with tiles
+    const Kern kern = kernels_of(c, kAdjointArrays);
+    const bool tiled = kern != Kern::cells;
     Timer tm{c, st};
     Inject<T> none;
     std::memset(&none, 0, sizeof none);
@@ -95,23 +106,23 @@ int adjoint_impl(fd3d_ctx *c, const fd3d_source *src, int nrec, const double *re
                     if (m > 0) Gv.f[VX + q] = (T *)(seg_slot(gws, GL, m - 1) + q * GL.fstep);
                 }
                 tm.begin(0);
-                launch_pass<T, false>(c, Gv, inj, n, kPassVel, st);
+                launch_pass<T, false>(c, kern, Gv, inj, n, kPassVel, st);
                 tm.end();
                 tm.begin(2);
-                launch_pass<T, false>(c, Gs, inj, n, kPassStress, st);
+                launch_pass<T, false>(c, kern, Gs, inj, n, kPassStress, st);
                 tm.end();
             } else {  // in place, also storing v^{n+1/2} in slot m
                 Grid<T> Gs = G;
                 for (int q = 0; q < 3; ++q) Gs.save[VX + q] = (T *)(slot + q * GL.fstep);
-                step<T, false>(c, Gs, inj, n, 0, taps, nullptr, st, tm);
+                step<T, false>(c, kern, Gs, inj, n, 0, taps, nullptr, st, tm);
             }
         }
         for (int n = n1 - 1; n >= n0; --n) {
             const int m = n - n0;
             if (tiled) {  // stress-B of step n + 1 and stress-A of step n in one pass
                 const AdjTiles<T> P = adj_tiles<T>(G, gws, GL, m);
-                launch_adj_pass<T>(c, P.g[0], none, n, kPassStressM, st, P.io[0]);
-                launch_adj_pass<T>(c, P.g[1], none, n, kPassVelA, st, P.io[1]);
+                launch_adj_pass<T>(c, kern, P.g[0], none, n, kPassStressM, st, P.io[0]);
+                launch_adj_pass<T>(c, kern, P.g[1], none, n, kPassVelA, st, P.io[1]);
                 inject(n, m);
             } else {
                 set_stored_velocity(A, gws, GL, m);
@@ -123,7 +134,7 @@ int adjoint_impl(fd3d_ctx *c, const fd3d_source *src, int nrec, const double *re
     }
     if (tiled) {  // stress-B of step 0, then the initial velocity's term of the b gradient
         const AdjTiles<T> P = adj_tiles<T>(G, gws, GL, 0);
-        launch_adj_pass<T>(c, P.g[2], none, 0, kPassStressB, st, P.io[2]);
+        launch_adj_pass<T>(c, kern, P.g[2], none, 0, kPassStressB, st, P.io[2]);
         launch_gb_initial<T>(G, A, gws, GL, st);
     }
     grad_finalize<T><<<grd, blk, 0, st>>>(G, A, g_lam, g_mu, g_rho);

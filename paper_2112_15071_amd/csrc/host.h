@@ -23,6 +23,7 @@
 #include "common.h"
 #include "fwd_cell.h"
 #include "fwd_tile.h"
+#include "row.h"
 #include "adj_cell.h"
 #include "util_kernels.h"
 
@@ -127,6 +128,7 @@ struct fd3d_ctx {
     int tile_x;   // columns of a tile (64, 128, 256)
     int tile_y;   // rows of a tile (4, 8, 16)
     int zchunk;   // z planes per workgroup sweep
+    bool auto_kernel;  // nothing selected yet: each operation picks rows or sweeps (kernels_of)
     // gradient state: checkpoints written by fd3d_forward_ckpt into a caller workspace
     const char *grad_ws;
     int grad_k;
@@ -290,6 +292,91 @@ inline bool window_ok(const fd3d_ctx *c, int zc)
     return planes * rows * (long)c->n[0] * (long)c->n[1] * (long)c->tsize <= kMaxWindowBytes;
 }
 
+// Tile workgroups of NT threads that the device runs at once: the tile kernels' registers
+// allow 20 waves a CU in FP32 (85 VGPRs), 12 in FP64.
+inline long tile_slots(int tsize, int nt)
+{
+    int dev = 0, cus = 256;
+    (void)hipGetDevice(&dev);
+    (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
+    return (long)std::max(1, (tsize == 8 ? 12 : 20) / (nt / 64)) * cus;
+}
+
+// Planes of a sweep when `tiles` columns of tiles of nz planes are cut into at most slots
+// workgroups (at least one per column, at least 4 planes).
+inline int sweep_depth(int nz, long tiles, long slots)
+{
+    const int cuts = (int)std::min<long>(nz, std::max<long>(1, slots / tiles));
+    return std::max(4, (nz + cuts - 1) / cuts);
+}
+
+// The row kernels address the planes around a cell (at most 9) through one buffer descriptor
+// per field; the cell variant of a context whose planes are too large for that runs the
+// kernels with a bounds test per load.
+inline bool rows_ok(const fd3d_ctx *c) { return window_ok(c, 1); }
+
+// Kernels of an operation that steps `arrays` cell-sized arrays: rows, tile sweeps, or the
+// kernels with a bounds test per load (cells).  A selected variant decides; with nothing
+// selected, the rows run while the arrays stay in the Infinity Cache, and else the sweeps.
+// Measured on both sides of the limit (FP32, MI355X, us per step, rows / best tile sweep): the
+// forward's 12 arrays at 192 x 192 x 128 (226 MB) 89 / 94 and 256 x 256 x 96 (302 MB) 156 / 133;
+// Born's 24 at 128^3 (201 MB) 74 / 94 and 192 x 160 x 128 (377 MB) 210 / 185; the adjoint's 29 at
+// 149 x 101 x 87 (152 MB) 159 / 183, 128^3 (243 MB) 201 / 202 and 192 x 160 x 128 (456 MB)
+// 380 / 369 (whole gradients).  FP64 rows hold twice the registers and halve the waves in
+// flight: 48^3 14.7 / 22.4, 120 x 112 x 104 (134 MB) 71 / 61.
+constexpr int kForwardArrays = 12, kBornArrays = 24, kAdjointArrays = 29;
+constexpr double kRowBytes32 = 230.0 * 1024 * 1024, kRowBytes64 = 64.0 * 1024 * 1024;
+enum class Kern { rows, tiles, cells };
+inline Kern kernels_of(const fd3d_ctx *c, int arrays)
+{
+    if (!c->auto_kernel)
+        return c->variant != FD3D_KERNEL_CELL ? Kern::tiles : rows_ok(c) ? Kern::rows : Kern::cells;
+    if (coarse_on(c->opts)) return Kern::tiles;
+    const double bytes = (double)arrays * c->n[0] * c->n[1] * c->n[2] * c->tsize;
+    return bytes <= (c->tsize == 8 ? kRowBytes64 : kRowBytes32) ? Kern::rows : Kern::tiles;
+}
+
+// Work of a row launch over a grid.  Blocks as wide as the rows, of the width that leaves the
+// fewest lanes idle (the widest of equals; 149 x 101 x 87: 32.8 us a step with 64 columns, 35.6
+// with 256).  Grids whose planes are small are cut into 8 slabs of planes, one per XCD: the few
+// planes that neighbouring cells share stay in its 4 MiB L2 (64^3: 10.3 us against 10.3 in 8
+// strips and 14.1 in 4).  Larger planes are cut into strips of at most 32 rows instead (256 x 256
+// x 72: 76.5 us against 111 in slabs; 200 x 150: 57 against 58, 256 x 128: 67 either way).
+constexpr long kSlabPlaneBytes = 128 << 10;
+// A launch over many shots (list) cuts its list of blocks into runs by itself: strips only.
+inline RowMap row_map(const fd3d_ctx *c, bool list = false)
+{
+    const int nx = c->n[0], ny = c->n[1], nz = c->n[2];
+    RowMap rm;
+    rm.lbx = 8;
+    for (int l = 7; l >= 6; --l) {
+        auto padded = [&](int b) { return ((nx + (1 << b) - 1) >> b) << b; };
+        if (padded(l) < padded(rm.lbx)) rm.lbx = l;
+    }
+    rm.ntx = (nx + (1 << rm.lbx) - 1) >> rm.lbx;
+    const int rows = 256 >> rm.lbx, blocks = (ny + rows - 1) / rows;
+    if ((long)nx * ny * c->tsize <= kSlabPlaneBytes) {
+        rm.nslab = 8;
+        rm.ns = 1;
+    } else {
+        rm.nslab = 1;
+        rm.ns = std::min(blocks, (std::max(8, (ny + 31) / 32) + 7) / 8 * 8);
+    }
+    rm.rps = (blocks + rm.ns - 1) / rm.ns;
+    rm.ns = (blocks + rm.rps - 1) / rm.rps;
+    if (list) rm.nslab = 1;
+    rm.np = (nz + rm.nslab - 1) / rm.nslab;
+    rm.cpx = (rm.ns * rm.nslab + 7) / 8;
+    return rm;
+}
+
+// Grid of a row launch that also samples nq receiver items.
+inline dim3 row_grid(const RowMap &rm, int nq = 0)
+{
+    const int per = 8 * rm.tiles() * 256;
+    return dim3(8, rm.tiles(), rm.planes() + (nq + per - 1) / per);
+}
+
 // Cache policy of a context's single-grid tile launches: the model arrays and the
 // gradient's stored velocities and accumulators are streamed (non-temporal) when the
 // grid's working set, nine fields and three model arrays, exceeds the 256 MB Infinity
@@ -302,12 +389,13 @@ inline bool stream_model(const fd3d_ctx *c)
     return 12.0 * (double)c->n[0] * (double)c->n[1] * (double)c->n[2] * (double)c->tsize > kInfinityCacheBytes;
 }
 
-// rec (stress passes of the forward only): the step's receiver sampling, carried by the
-// tile launch or launched after the cell kernel.  Forward passes (velocity, stress and
+// rec (stress passes of the forward only): the
+// step's receiver sampling, carried by the row or tile launch or launched after the cell
+// kernel.  Forward passes (velocity, stress and
 // their storing variants); defined for float and double, with and without free surface.
 template <typename T, bool FS>
-void launch_pass(const fd3d_ctx *c, const Grid<T> &G, const Inject<T> &inj, int n, int pass, hipStream_t st,
-                 const TileIO<T> &io = TileIO<T>{}, const RecJob<T> &rec = RecJob<T>{});
+void launch_pass(const fd3d_ctx *c, Kern kern, const Grid<T> &G, const Inject<T> &inj, int n, int pass, hipStream_t st,
+                 const RecJob<T> &rec = RecJob<T>{});
 
 // The receiver sampling of a grid's velocity (none when nrec is 0).
 template <typename T> RecJob<T> rec_job(const T *vx, const T *vy, const T *vz, const RecTap<T> *taps, int nrec,
@@ -327,8 +415,8 @@ template <typename T> RecJob<T> rec_job(const T *vx, const T *vy, const T *vz, c
 
 // One forward step: velocity pass, then the stress pass, which samples the receivers.
 template <typename T, bool FS>
-void step(fd3d_ctx *c, const Grid<T> &G, const Inject<T> &inj, int n, int nrec, const RecTap<T> *taps, T *traces,
-          hipStream_t st, Timer &tm);
+void step(fd3d_ctx *c, Kern kern, const Grid<T> &G, const Inject<T> &inj, int n, int nrec, const RecTap<T> *taps,
+          T *traces, hipStream_t st, Timer &tm);
 
 // Fused tile shapes: FP32 64x4 and 64x8, FP64 64x4.
 bool fused_supported(const fd3d_ctx *c, int tx, int ty);
