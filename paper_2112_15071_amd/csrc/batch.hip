@@ -24,7 +24,8 @@ struct BatchGroup {
     int tx, ty, tx2, ty2;
     int vac;  // some shot of the group has a vacuum surface
     long cols;  // columns of tiles over all shots of the launch
-    int rows, rtiles;  // row kernels, and their blocks
+    int rtiles;              // row kernels: their blocks
+    const ShotRows *rows;    // and the shots' shares of them (null: tile kernels)
     int ntp;  // cache policy of the group's forward passes (see group_streams)
 };
 
@@ -34,7 +35,7 @@ struct fd3d_batch {
     int tsize, nt, fs;
     char *ws;
     size_t ws_bytes;
-    size_t off_fwd, off_rec;
+    size_t off_fwd, off_rec, off_rows;
     int tile_x, tile_y, wgs_req;
     int tile2_x, tile2_y;  // optional second tile shape (same workgroup size), 0: none
     bool tiles_set;        // the caller or the tuner selected the batch's tile shapes
@@ -42,6 +43,7 @@ struct fd3d_batch {
     std::vector<BatchGroup> groups;
     std::vector<int> order;  // shot at each position of the descriptor arrays
     std::vector<unsigned char> fwd_host, rec_host;
+    std::vector<ShotRows> rows_host;
     hipEvent_t staged;
     bool staged_pending;
     hipStream_t cap;
@@ -58,7 +60,8 @@ size_t batch_desc_bytes(int nshot, int tsize)
 {
     const size_t f = tsize == 8 ? sizeof(ShotFwd<double>) : sizeof(ShotFwd<float>);
     const size_t r = tsize == 8 ? sizeof(ShotRec<double>) : sizeof(ShotRec<float>);
-    return round_up((size_t)nshot * f, kAlign) + round_up((size_t)nshot * r, kAlign);
+    return round_up((size_t)nshot * f, kAlign) + round_up((size_t)nshot * r, kAlign) +
+           round_up((size_t)nshot * sizeof(ShotRows), kAlign);
 }
 
 // Supported pairs of batch tile shapes (primary, second; equal workgroup sizes): FP32
@@ -205,6 +208,9 @@ bool batch_rows(const fd3d_ctx *const *ctx, int ns, int arrays)
     return bytes <= (ctx[0]->tsize == 8 ? kRowBytes64 : kRowBytes32);
 }
 
+// Where the batch workspace holds the shots' row maps.
+const ShotRows *batch_row_maps(const fd3d_batch *b) { return (const ShotRows *)(b->ws + b->off_rows); }
+
 // One pass over a group with the row kernels.
 template <typename T, bool FS>
 void launch_rows_multi(const BatchGroup &gr, const ShotFwd<T> *d, int n, int pass, hipStream_t st, const ShotRec<T> *r, int nt)
@@ -214,21 +220,21 @@ void launch_rows_multi(const BatchGroup &gr, const ShotFwd<T> *d, int n, int pas
     const int gs = g + rec_blocks(rec, 256);
     if constexpr (!FS) {
         if (gr.vac && pass == kPassVel) {
-            vel_row_multi<T, false, kFwd, true><<<g, 256, 0, st>>>(d, S, W, n);
+            vel_row_multi<T, false, kFwd, true><<<g, 256, 0, st>>>(d, gr.rows, S, W, n);
             return;
         }
         if (gr.vac && pass == kPassStress) {
-            stress_row_multi<T, false, kFwd, true><<<gs, 256, 0, st>>>(d, S, W, n, rec);
+            stress_row_multi<T, false, kFwd, true><<<gs, 256, 0, st>>>(d, gr.rows, S, W, n, rec);
             return;
         }
     }
     switch (pass) {
-    case kPassVel: vel_row_multi<T, FS, kFwd, false><<<g, 256, 0, st>>>(d, S, W, n); break;
-    case kPassStress: stress_row_multi<T, FS, kFwd, false><<<gs, 256, 0, st>>>(d, S, W, n, rec); break;
-    case kPassVelSave: vel_row_multi<T, false, kFwdSave, false><<<g, 256, 0, st>>>(d, S, W, n); break;
-    case kPassStressM: stress_row_multi<T, false, kAdjM, false><<<g, 256, 0, st>>>(d, S, W, n, rec); break;
-    case kPassVelA: vel_row_multi<T, false, kAdjA, false><<<g, 256, 0, st>>>(d, S, W, n); break;
-    default: stress_row_multi<T, false, kAdjB, false><<<g, 256, 0, st>>>(d, S, W, n, rec); break;
+    case kPassVel: vel_row_multi<T, FS, kFwd, false><<<g, 256, 0, st>>>(d, gr.rows, S, W, n); break;
+    case kPassStress: stress_row_multi<T, FS, kFwd, false><<<gs, 256, 0, st>>>(d, gr.rows, S, W, n, rec); break;
+    case kPassVelSave: vel_row_multi<T, false, kFwdSave, false><<<g, 256, 0, st>>>(d, gr.rows, S, W, n); break;
+    case kPassStressM: stress_row_multi<T, false, kAdjM, false><<<g, 256, 0, st>>>(d, gr.rows, S, W, n, rec); break;
+    case kPassVelA: vel_row_multi<T, false, kAdjA, false><<<g, 256, 0, st>>>(d, gr.rows, S, W, n); break;
+    default: stress_row_multi<T, false, kAdjB, false><<<g, 256, 0, st>>>(d, gr.rows, S, W, n, rec); break;
     }
 }
 
@@ -345,7 +351,7 @@ void make_groups(fd3d_batch *b)
     BatchGroup all = whole_batch(b);
     if (b->group_bytes == 0) {
         all.cols = tile_columns(all, b->nshot, [&](int q) { return b->ctx[q]; });
-        all.rows = !b->tiles_set && batch_rows(b->ctx.data(), b->nshot, kForwardArrays);
+        if (!b->tiles_set && batch_rows(b->ctx.data(), b->nshot, kForwardArrays)) all.rows = batch_row_maps(b);
         b->groups.push_back(all);
         return;
     }
@@ -363,7 +369,7 @@ void make_groups(fd3d_batch *b)
         std::vector<const fd3d_ctx *> members;
         for (int q = s; q < e; ++q) members.push_back(ctx_at(q));
         g.ntp = group_streams(members.data(), g.ns);
-        g.rows = batch_rows(members.data(), g.ns, kForwardArrays);
+        if (batch_rows(members.data(), g.ns, kForwardArrays)) g.rows = batch_row_maps(b) + g.s0;
         const fd3d_ctx *c0 = ctx_at(s);
         auto tiled = [](const fd3d_ctx *c) { return c->variant == FD3D_KERNEL_TILE || c->auto_kernel; };
         bool same = tiled(c0);
@@ -386,6 +392,7 @@ int batch_forward_impl(fd3d_batch *b, const fd3d_source *srcs, const int *nrec, 
 {
     std::vector<ShotFwd<T>> fw(b->nshot);
     std::vector<ShotRec<T>> rr(b->nshot);
+    std::vector<ShotRows> maps(b->nshot);
     make_groups(b);
     size_t gi = 0;
     int tiles = 0, recs = 0, rtiles = 0;
@@ -409,9 +416,8 @@ int batch_forward_impl(fd3d_batch *b, const fd3d_source *srcs, const int *nrec, 
         fw[p].tm = tm;
         fw[p].base = tiles;
         tiles += tm.ntx * tm.nty * tm.nzc;
-        fw[p].rm = row_map(c, true);
-        fw[p].rbase = rtiles;
-        rtiles += fw[p].rm.ns * fw[p].rm.tiles() * fw[p].rm.np;
+        maps[p] = ShotRows{row_map(c, true), rtiles};
+        rtiles += maps[p].rm.ns * maps[p].rm.tiles() * maps[p].rm.np;
         for (int q = 0; q < 3; ++q) rr[p].v[q] = fw[p].G.f[VX + q];
         rr[p].taps = (const RecTap<T> *)(c->ws + c->L.rec);
         rr[p].traces = nr ? (T *)traces[s] : nullptr;
@@ -432,7 +438,10 @@ int batch_forward_impl(fd3d_batch *b, const fd3d_source *srcs, const int *nrec, 
     b->fwd_host.assign((const unsigned char *)fw.data(), (const unsigned char *)(fw.data() + b->nshot));
     b->rec_host.assign((const unsigned char *)rr.data(), (const unsigned char *)(rr.data() + b->nshot));
     HIP_TRY(hipMemcpyAsync(b->ws + b->off_fwd, b->fwd_host.data(), b->fwd_host.size(), hipMemcpyHostToDevice, st));
+    b->rows_host = maps;
     HIP_TRY(hipMemcpyAsync(b->ws + b->off_rec, b->rec_host.data(), b->rec_host.size(), hipMemcpyHostToDevice, st));
+    HIP_TRY(hipMemcpyAsync(b->ws + b->off_rows, b->rows_host.data(), maps.size() * sizeof(ShotRows), hipMemcpyHostToDevice,
+                           st));
     HIP_TRY(hipEventRecord(b->staged, st));
     b->staged_pending = true;
 
@@ -450,7 +459,7 @@ int batch_forward_impl(fd3d_batch *b, const fd3d_source *srcs, const int *nrec, 
         wgs = std::min(wgs, ((g.tiles + 7) / 8) * 8);
         g.wgs = std::max(8, (wgs + 7) / 8 * 8);
         for (long v : {(long)g.s0, (long)g.ns, (long)g.tiles, (long)g.recs, (long)g.wgs, (long)g.tx, (long)g.ty,
-                       (long)g.tx2, (long)g.ty2, (long)g.vac, (long)g.rows, (long)g.rtiles})
+                       (long)g.tx2, (long)g.ty2, (long)g.vac, (long)(g.rows != nullptr), (long)g.rtiles})
             mix(v);
     }
     if (!use_graph) return batch_sequence<T>(b, flags, st);
@@ -539,6 +548,7 @@ int batch_gradient_impl(fd3d_batch *b, const fd3d_source *srcs, const int *nrec,
     std::vector<GradLayout> GL(S);
     std::vector<ShotFwd<T>> fw(S);
     std::vector<ShotRec<T>> rr(S);
+    std::vector<ShotRows> maps(S);
     std::vector<ShotInject<T>> ij(S);
     std::vector<AdjGrid<T>> ag(S);
     int tiles = 0, rtiles = 0, recs = 0, ncol = 0;
@@ -570,9 +580,8 @@ int batch_gradient_impl(fd3d_batch *b, const fd3d_source *srcs, const int *nrec,
         fw[s].tm = tm;
         fw[s].base = tiles;
         tiles += tm.ntx * tm.nty * tm.nzc;
-        fw[s].rm = row_map(c, true);
-        fw[s].rbase = rtiles;
-        rtiles += fw[s].rm.ns * fw[s].rm.tiles() * fw[s].rm.np;
+        maps[s] = ShotRows{row_map(c, true), rtiles};
+        rtiles += maps[s].rm.ns * maps[s].rm.tiles() * maps[s].rm.np;
         for (int q = 0; q < 3; ++q) rr[s].v[q] = fw[s].G.f[VX + q];
         rr[s].taps = (const RecTap<T> *)(c->ws + c->L.rec);
         rr[s].traces = (T *)traces[s];
@@ -648,7 +657,10 @@ int batch_gradient_impl(fd3d_batch *b, const fd3d_source *srcs, const int *nrec,
     }
     b->rec_host.assign((const unsigned char *)rr.data(), (const unsigned char *)(rr.data() + S));
     HIP_TRY(hipMemcpyAsync(bws, h, BL.total, hipMemcpyHostToDevice, st));
+    b->rows_host = maps;
     HIP_TRY(hipMemcpyAsync(b->ws + b->off_rec, b->rec_host.data(), b->rec_host.size(), hipMemcpyHostToDevice, st));
+    HIP_TRY(hipMemcpyAsync(b->ws + b->off_rows, b->rows_host.data(), maps.size() * sizeof(ShotRows), hipMemcpyHostToDevice,
+                           st));
     HIP_TRY(hipEventRecord(b->staged, st));
     b->staged_pending = true;
 
@@ -662,8 +674,8 @@ int batch_gradient_impl(fd3d_batch *b, const fd3d_source *srcs, const int *nrec,
     all.rtiles = rtiles;
     all.recs = recs;
     BatchGroup fwd = all;
-    fwd.rows = !b->tiles_set && batch_rows(b->ctx.data(), S, kForwardArrays);
-    all.rows = !b->tiles_set && batch_rows(b->ctx.data(), S, kAdjointArrays);
+    if (!b->tiles_set && batch_rows(b->ctx.data(), S, kForwardArrays)) fwd.rows = batch_row_maps(b);
+    if (!b->tiles_set && batch_rows(b->ctx.data(), S, kAdjointArrays)) all.rows = batch_row_maps(b);
 
     const bool merged = all.rows || all.tx2 == 0;  // stress-M (row kernels, or one tile shape)
     // forward with checkpoints
@@ -780,6 +792,7 @@ int fd3d_batch_create(fd3d_batch **out, int nshot, fd3d_ctx *const *ctxs, void *
     b->ws_bytes = ws_bytes;
     b->off_fwd = 0;
     b->off_rec = round_up((size_t)nshot * (b->tsize == 8 ? sizeof(ShotFwd<double>) : sizeof(ShotFwd<float>)), kAlign);
+    b->off_rows = b->off_rec + round_up((size_t)nshot * (b->tsize == 8 ? sizeof(ShotRec<double>) : sizeof(ShotRec<float>)), kAlign);
     // tile shape of the batch: the widest default among the shots that every shot supports
     int minx = ctxs[0]->n[0];
     for (int s = 1; s < nshot; ++s) minx = std::min(minx, ctxs[s]->n[0]);

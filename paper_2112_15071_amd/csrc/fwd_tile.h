@@ -28,21 +28,6 @@ struct TileMap {
     int ntx, nty, nzc, zc;
 };
 
-// Work of a row launch: blocks of 256 threads, 1 << lbx (64, 128 or 256) columns by 256 >> lbx
-// rows of one plane.  The grid is cut into ns strips of rps row blocks along y and nslab slabs
-// of np planes along z; a piece (strip of a slab) is walked plane by plane.  Each of the 8 XCDs
-// takes the cpx pieces [x cpx, (x + 1) cpx), one after the other.
-struct RowMap {
-    int ntx;  // column blocks
-    int lbx;
-    int rps;
-    int ns, nslab, np, cpx;
-
-    // blocks of one plane of a piece, and planes of an XCD's pieces
-    __host__ __device__ int tiles() const { return rps * ntx; }
-    __host__ __device__ int planes() const { return np * cpx; }
-};
-
 typedef __amdgpu_buffer_rsrc_t rsrc_t;
 
 constexpr unsigned kOOB = 0x80000000u;  // byte offset past every plane (< 2 GiB per plane)
@@ -1246,8 +1231,6 @@ template <typename T> struct ShotFwd {
     TileMap tm;
     int base;  // first work item of this shot
     int alt;   // the batch's second tile shape covers this shot
-    RowMap rm;  // row launches: the shot's blocks, and the first of them in the launch's list
-    int rbase;
 };
 
 // Work item range [lo, hi) and stride of this workgroup in the XCD-chunked order of a

@@ -26,6 +26,21 @@
 
 namespace fd3d {
 
+// Work of a row launch: blocks of 256 threads, 1 << lbx (64, 128 or 256) columns by 256 >> lbx
+// rows of one plane.  The grid is cut into ns strips of rps row blocks along y and nslab slabs
+// of np planes along z; a piece (strip of a slab) is walked plane by plane.  Each of the 8 XCDs
+// takes the cpx pieces [x cpx, (x + 1) cpx), one after the other.
+struct RowMap {
+    int ntx;  // column blocks
+    int lbx;
+    int rps;
+    int ns, nslab, np, cpx;
+
+    // blocks of one plane of a piece, and planes of an XCD's pieces
+    __host__ __device__ int tiles() const { return rps * ntx; }
+    __host__ __device__ int planes() const { return np * cpx; }
+};
+
 // Cell of a lane; row and plane are uniform over its wave.  k = nz: no work.
 struct RowPos {
     int i, j, k;
@@ -465,28 +480,35 @@ __global__ void __launch_bounds__(256) stress_row_io(Grid<T> G, Inject<T> src, i
 // run of XCD b mod 8 (the passes that walk backwards count from the last).  Runs rather than 8
 // slabs of every shot: four shots of 96 x 80 x 72, forward step 56.4 us
 // against 57.6; 40 x 50 x 60 by six: 30.3 against 31.3.
+struct ShotRows {  // a shot's blocks, and the first of them in the list
+    RowMap rm;
+    int base;
+};
+
 template <typename T>
-__device__ __forceinline__ const ShotFwd<T> &row_shot(const ShotFwd<T> *shots, int *s_base, int nshot, int total,
-                                                      bool reverse, RowPos &p)
+__device__ __forceinline__ const ShotFwd<T> &row_shot(const ShotFwd<T> *shots, const ShotRows *rows, int *s_base, int nshot,
+                                                      int total, bool reverse, RowPos &p)
 {
-    load_bases(s_base, &shots[0].rbase, base_stride<ShotFwd<T>>(), nshot);
+    load_bases(s_base, &rows[0].base, base_stride<ShotRows>(), nshot);
     const int per = (total + 7) / 8, q = (int)blockIdx.x >> 3;
     const int at = ((int)blockIdx.x & 7) * per + (reverse ? per - 1 - q : q);
     const int l = at < total ? at : total - 1;  // past the last block: no work (below)
-    const ShotFwd<T> &d = shots[shot_of(s_base, nshot, l)];
-    const RowMap rm = d.rm;
-    const int b = l - d.rbase, strip = rm.ns > 1 ? b / (rm.tiles() * rm.np) : 0, r = b - strip * rm.tiles() * rm.np;
+    const int s = shot_of(s_base, nshot, l);
+    const ShotFwd<T> &d = shots[s];
+    const RowMap rm = rows[s].rm;
+    const int b = l - rows[s].base, strip = rm.ns > 1 ? b / (rm.tiles() * rm.np) : 0, r = b - strip * rm.tiles() * rm.np;
     const int z = r / rm.tiles();
     p = row_cell(rm, strip, r - z * rm.tiles(), at < total ? z : d.G.nz);
     return d;
 }
 
 template <typename T, bool FS, int MODE, bool VAC>
-__global__ void __launch_bounds__(256) vel_row_multi(const ShotFwd<T> *__restrict__ shots, int nshot, int total, int n)
+__global__ void __launch_bounds__(256) vel_row_multi(const ShotFwd<T> *__restrict__ shots,
+                                                     const ShotRows *__restrict__ rows, int nshot, int total, int n)
 {
     __shared__ int s_base[kMaxShots];
     RowPos p;
-    const ShotFwd<T> &d = row_shot(shots, s_base, nshot, total, vel_sweeps_up<MODE>(), p);
+    const ShotFwd<T> &d = row_shot(shots, rows, s_base, nshot, total, vel_sweeps_up<MODE>(), p);
     const Grid<T> G = d.G;
     const Inject<T> src = d.src;
     const TileIO<T> io = d.io;
@@ -494,7 +516,8 @@ __global__ void __launch_bounds__(256) vel_row_multi(const ShotFwd<T> *__restric
 }
 
 template <typename T, bool FS, int MODE, bool VAC>
-__global__ void __launch_bounds__(256) stress_row_multi(const ShotFwd<T> *__restrict__ shots, int nshot, int total, int n,
+__global__ void __launch_bounds__(256) stress_row_multi(const ShotFwd<T> *__restrict__ shots,
+                                                        const ShotRows *__restrict__ rows, int nshot, int total, int n,
                                                         RecMulti<T> rec)
 {
     __shared__ int s_base[kMaxShots];
@@ -503,7 +526,7 @@ __global__ void __launch_bounds__(256) stress_row_multi(const ShotFwd<T> *__rest
         return;
     }
     RowPos p;
-    const ShotFwd<T> &d = row_shot(shots, s_base, nshot, total, stress_sweeps_up<MODE>(), p);
+    const ShotFwd<T> &d = row_shot(shots, rows, s_base, nshot, total, stress_sweeps_up<MODE>(), p);
     const Grid<T> G = d.G;
     const Inject<T> src = d.src;
     const TileIO<T> io = d.io;
