@@ -426,7 +426,7 @@ template <typename T> __global__ void __launch_bounds__(256) copy_multi(const Co
 }
 
 // Residual r = d - d_obs of one shot's traces and per-block partial sums of r^2 / 2
-// (deterministic two-stage reduction: misfit_final adds the partials in order).
+// (deterministic two-stage reduction: misfit_final adds the partials in a fixed order).
 template <typename T>
 __global__ void __launch_bounds__(256) residual_misfit(const T *__restrict__ d, const T *__restrict__ obs,
                                                        T *__restrict__ r, long n, double *__restrict__ part)
@@ -447,13 +447,15 @@ __global__ void __launch_bounds__(256) residual_misfit(const T *__restrict__ d, 
     if (threadIdx.x == 0) part[blockIdx.x] = sh[0];
 }
 
+// One wave: each lane adds every 64th partial, the lanes in a fixed tree (one thread adding
+// them in turn waited 30 us for its loads).
 template <typename T>
 __global__ void __launch_bounds__(64) misfit_final(const double *__restrict__ part, int nb, T *__restrict__ out)
 {
-    if (threadIdx.x != 0 || blockIdx.x != 0) return;
     double s = 0.0;
-    for (int b = 0; b < nb; ++b) s += part[b];
-    out[0] = (T)(0.5 * s);
+    for (int b = threadIdx.x; b < nb; b += 64) s += part[b];
+    for (int w = 32; w > 0; w >>= 1) s += __shfl_down(s, w);
+    if (threadIdx.x == 0) out[0] = (T)(0.5 * s);
 }
 
 } // namespace fd3d

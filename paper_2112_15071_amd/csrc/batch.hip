@@ -453,6 +453,7 @@ int batch_forward_impl(fd3d_batch *b, const fd3d_source *srcs, const int *nrec, 
     uint64_t key = 1469598103934665603ull;
     auto mix = [&](long v) { key = (key ^ (uint64_t)v) * 1099511628211ull; };
     mix(flags & FD3D_KEEP_STATE);
+    for (const fd3d_ctx *c : b->ctx) mix(c->cur);  // the state copy that the sequence zeroes
     for (BatchGroup &g : b->groups) {
         const int occ = b->fs ? multi_occupancy<T, true>(g) : multi_occupancy<T, false>(g);
         int wgs = b->wgs_req > 0 ? b->wgs_req : cus * occ;
@@ -511,7 +512,7 @@ template <typename T> BatchGradLayout make_batch_grad_layout(const fd3d_batch *b
     L.nseg = (b->nt + k - 1) / k;
     L.fwd_bytes = round_up((size_t)b->nshot * sizeof(ShotFwd<T>), kAlign);
     L.inj_bytes = round_up((size_t)b->nshot * sizeof(ShotInject<T>), kAlign);
-    L.copy_bytes = round_up((size_t)b->nshot * 9 * sizeof(CopyDesc<T>), kAlign);
+    L.copy_bytes = round_up((size_t)b->nshot * sizeof(CopyDesc<float4>), kAlign);
     size_t off = 0;
     L.fwd0 = off;
     off += L.fwd_bytes;
@@ -642,18 +643,16 @@ int batch_gradient_impl(fd3d_batch *b, const fd3d_source *srcs, const int *nrec,
     }
     std::memcpy(h + BL.sb, sb.data(), fbytes);
     for (int cidx = 0; cidx < BL.nseg; ++cidx) {
-        std::vector<CopyDesc<T>> sv(S * 9), rs(S * 9);
+        std::vector<CopyDesc<float4>> sv(S), rs(S);  // whole groups, in 16-byte words
         for (int s = 0; s < S; ++s) {
-            char *ck = (char *)gws[s] + GL[s].ckpt + (size_t)cidx * GL[s].group;
-            const long n = (long)(b->ctx[s]->L.field_bytes / sizeof(T));
-            for (int q = 0; q < NFIELD; ++q) {
-                T *live = (T *)state_chunk<T>(b->ctx[s], fw[s].G, q), *kept = (T *)(ck + q * GL[s].chunk);
-                sv[s * 9 + q] = CopyDesc<T>{live, kept, n};
-                rs[s * 9 + q] = CopyDesc<T>{kept, live, n};
-            }
+            float4 *kept = (float4 *)((char *)gws[s] + GL[s].ckpt + (size_t)cidx * GL[s].group);
+            float4 *live = (float4 *)fw[s].G.f[0];
+            const long n = (long)(GL[s].group / sizeof(float4));
+            sv[s] = CopyDesc<float4>{live, kept, n};
+            rs[s] = CopyDesc<float4>{kept, live, n};
         }
-        std::memcpy(h + BL.save_copy + cidx * BL.copy_bytes, sv.data(), sv.size() * sizeof(CopyDesc<T>));
-        std::memcpy(h + BL.rest_copy + cidx * BL.copy_bytes, rs.data(), rs.size() * sizeof(CopyDesc<T>));
+        std::memcpy(h + BL.save_copy + cidx * BL.copy_bytes, sv.data(), sv.size() * sizeof(CopyDesc<float4>));
+        std::memcpy(h + BL.rest_copy + cidx * BL.copy_bytes, rs.data(), rs.size() * sizeof(CopyDesc<float4>));
     }
     b->rec_host.assign((const unsigned char *)rr.data(), (const unsigned char *)(rr.data() + S));
     HIP_TRY(hipMemcpyAsync(bws, h, BL.total, hipMemcpyHostToDevice, st));
@@ -681,7 +680,7 @@ int batch_gradient_impl(fd3d_batch *b, const fd3d_source *srcs, const int *nrec,
     // forward with checkpoints
     auto desc = [&](size_t off) { return (const ShotFwd<T> *)(bws + off); };
     const ShotRec<T> *rdesc = (const ShotRec<T> *)(b->ws + b->off_rec);
-    const dim3 cgrid(256, 9 * S);
+    const dim3 cgrid(1024, S);
     if (!(flags & FD3D_KEEP_STATE))
         for (fd3d_ctx *c : b->ctx) zero_fields<T>(c, st);
     auto pass = [&](const ShotFwd<T> *d, int n, int p, const ShotRec<T> *r = nullptr) {
@@ -689,7 +688,7 @@ int batch_gradient_impl(fd3d_batch *b, const fd3d_source *srcs, const int *nrec,
     };
     for (int n = 0; n < b->nt; ++n) {
         if (n % k == 0)
-            copy_multi<T><<<cgrid, 256, 0, st>>>((const CopyDesc<T> *)(bws + BL.save_copy + (n / k) * BL.copy_bytes));
+            copy_multi<float4><<<cgrid, 256, 0, st>>>((const CopyDesc<float4> *)(bws + BL.save_copy + (n / k) * BL.copy_bytes));
         multi_pass<T, false>(fwd, desc(BL.fwd0), n, kPassVel, st);
         pass(desc(BL.fwd0), n, kPassStress, rdesc);  // also samples the receivers
     }
@@ -702,12 +701,12 @@ int batch_gradient_impl(fd3d_batch *b, const fd3d_source *srcs, const int *nrec,
         residual_misfit<T><<<kReduceBlocks, 256, 0, st>>>((const T *)traces[s], (const T *)d_obs[s], res, nn, part);
         misfit_final<T><<<1, 64, 0, st>>>(part, kReduceBlocks,
                                           misfit && misfit[s] ? (T *)misfit[s] : (T *)((char *)gws[s] + GL[s].misfit));
-        zero_grad_fields<T>((char *)gws[s], GL[s], st);
+        zero_grad_fields<T>(fw[s].G, (char *)gws[s], GL[s], st);
     }
     // reverse sweep over the segments
     for (int sg = BL.nseg - 1; sg >= 0; --sg) {
         const int n0 = sg * k, n1 = std::min(n0 + k, b->nt);
-        copy_multi<T><<<cgrid, 256, 0, st>>>((const CopyDesc<T> *)(bws + BL.rest_copy + sg * BL.copy_bytes));
+        copy_multi<float4><<<cgrid, 256, 0, st>>>((const CopyDesc<float4> *)(bws + BL.rest_copy + sg * BL.copy_bytes));
         for (int n = n0; n < n1; ++n) {
             pass(desc(BL.fwd_slot + (n - n0) * BL.fwd_bytes), n, kPassVelSave);
             pass(desc(BL.fst_slot + (n - n0) * BL.fwd_bytes), n, kPassStress);

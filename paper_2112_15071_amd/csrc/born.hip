@@ -22,12 +22,10 @@ int born_impl(fd3d_ctx *c, fd3d_ctx *dc, const fd3d_source *src, const void *dla
     zero_fields<T>(c, st);
     zero_fields<T>(dc, st);
     if (c->L.rows) {  // the perturbation into rows 3-5 of the model block, beside the model
-        const void *in[3] = {dlam, dmu, drho};
+        const T *in[3] = {(const T *)dlam, (const T *)dmu, (const T *)drho};
         T *row[3];
-        for (int q = 0; q < 3; ++q) {
-            row[q] = (T *)(c->ws + c->L.model + (3 + q) * c->L.fstep);
-            copy_field<T>(c, row[q], true, (const T *)in[q], false, -1, st);
-        }
+        for (int q = 0; q < 3; ++q) row[q] = (T *)(c->ws + c->L.model + (3 + q) * c->L.fstep);
+        copy_arrays<T>(c, 3, row, true, in, false, -1, st);
         dlam = row[0];
         dmu = row[1];
         drho = row[2];

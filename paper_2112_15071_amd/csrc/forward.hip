@@ -203,12 +203,8 @@ int forward_impl(fd3d_ctx *c, const fd3d_source *src, int nrec, const double *re
     c->prof_used = 0;
     for (int n = 0; n < c->nt; ++n) {
         const Grid<T> G = make_grid<T>(c);
-        if (GL && n % GL->k == 0) {
-            char *dst = gws + GL->ckpt + (size_t)(n / GL->k) * GL->group;
-            for (int q = 0; q < NFIELD; ++q)
-                HIP_TRY(hipMemcpyAsync(dst + q * GL->chunk, state_chunk<T>(c, G, q), c->L.field_bytes,
-                                       hipMemcpyDeviceToDevice, st));
-        }
+        if (GL && n % GL->k == 0)
+            copy_group(c, gws + GL->ckpt + (size_t)(n / GL->k) * GL->group, (const char *)G.f[0], st);
         if (fused && c->opts.free_surface) fused_step<T, true>(c, inj, n, nrec, taps, (T *)traces, st, tm);
         else if (fused) fused_step<T, false>(c, inj, n, nrec, taps, (T *)traces, st, tm);
         else if (c->opts.free_surface) step<T, true>(c, kern, G, inj, n, nrec, taps, (T *)traces, st, tm);

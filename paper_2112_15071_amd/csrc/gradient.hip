@@ -62,7 +62,7 @@ int adjoint_impl(fd3d_ctx *c, const fd3d_source *src, int nrec, const double *re
     if (rc) return rc;
     Grid<T> G = make_grid<T>(c);
     AdjGrid<T> A = make_adj<T>(gws, GL);
-    zero_grad_fields<T>(gws, GL, st);
+    zero_grad_fields<T>(G, gws, GL, st);
     const RecTap<T> *taps = (const RecTap<T> *)(c->ws + c->L.rec);
     const int *colors = (const int *)(c->ws + c->L.colors);
     const dim3 blk(64, 4, 1), grd((G.nx + 63) / 64, (G.ny + 3) / 4, G.nz);
@@ -91,11 +91,9 @@ int adjoint_impl(fd3d_ctx *c, const fd3d_source *src, int nrec, const double *re
     for (int sgi = GL.nseg - 1; sgi >= 0; --sgi) {
         const int n0 = sgi * GL.k, n1 = std::min(n0 + GL.k, c->nt);
         const char *ck = gws + GL.ckpt + (size_t)sgi * GL.group;
-        for (int q = 0; q < NFIELD; ++q)
-            HIP_TRY(hipMemcpyAsync(state_chunk<T>(c, G, q), ck + q * GL.chunk, c->L.field_bytes,
-                                   hipMemcpyDeviceToDevice, st));
+        copy_group(c, (char *)G.f[0], ck, st);
         if (!tiled)  // the cell adjoint's v^{n-1/2} of the segment's first step
-            HIP_TRY(hipMemcpyAsync(gws + GL.prev, ck, prev_copy_bytes(c, GL), hipMemcpyDeviceToDevice, st));
+            copy_group(c, gws + GL.prev, ck, st);
         for (int n = n0; n < n1; ++n) {
             const int m = n - n0;
             char *slot = seg_slot(gws, GL, m);
@@ -154,7 +152,6 @@ GradLayout make_grad_layout(const fd3d_ctx *c, int k)
     g.nseg = (c->nt + k - 1) / k;
     g.fstep = c->L.fstep;
     g.group = c->L.group;
-    g.chunk = c->L.chunk;
     size_t off = 0;
     g.adj = off;
     off += g.group;
@@ -304,11 +301,15 @@ int fd3d_get_adjoint_state(fd3d_ctx *ctx, const void *gws, void *const fields[9]
                 scale_velocity<float><<<grd, blk, 0, st>>>(make_grid<float>(ctx), (const float *)a, f, (float *)fields[f]);
         } else if (!ctx->L.rows) {
             HIP_TRY(hipMemcpyAsync(fields[f], a, ctx->L.field_bytes, hipMemcpyDeviceToDevice, st));
-        } else if (ctx->tsize == 8) {
-            copy_field<double>(ctx, (double *)fields[f], false, (const double *)a, true, -1, st);
-        } else {
-            copy_field<float>(ctx, (float *)fields[f], false, (const float *)a, true, -1, st);
         }
+    }
+    if (ctx->L.rows) {  // A_s, in one launch
+        const char *a[6];
+        for (int q = 0; q < 6; ++q) a[q] = (const char *)gws + GL.adj + (SXX + q) * GL.fstep;
+        if (ctx->tsize == 8)
+            copy_arrays<double>(ctx, 6, (double *const *)(fields + SXX), false, (const double *const *)a, true, -1, st);
+        else
+            copy_arrays<float>(ctx, 6, (float *const *)(fields + SXX), false, (const float *const *)a, true, -1, st);
     }
     HIP_TRY(hipGetLastError());
     return FD3D_OK;

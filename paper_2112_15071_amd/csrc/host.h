@@ -76,7 +76,6 @@ struct Layout {
     size_t field_bytes;     // bytes of one field's samples
     size_t fstep;           // bytes from one field of a group to the next
     size_t group;           // bytes of a group of up to nine fields
-    size_t chunk;           // bytes from one field-sized chunk of a group to the next (copies)
 };
 
 // Workspace layout of a grid under the given options (field storage chosen by opts.layout).
@@ -173,25 +172,51 @@ template <typename T> Grid<T> make_grid(const fd3d_ctx *c)
     return G;
 }
 
-// Both state copies (the first bytes of the workspace; not the model block after them).
+// The current state copy.  (The other one needs no fill: the fused step that writes it stores
+// every sample.)
 template <typename T> void zero_fields(fd3d_ctx *c, hipStream_t st)
 {
-    fill_zero<T><<<2048, 256, 0, st>>>((T *)c->ws, (long)(2 * c->L.group / sizeof(T)));
+    fill_zero<T><<<2048, 256, 0, st>>>((T *)(c->ws + c->L.field[c->cur][0]), (long)(c->L.group / sizeof(T)));
 }
 
-// Strided copy of field-shaped arrays between node arrays (x fastest, unpadded) and the
-// workspace's field storage, pinned slots of component `comp` zeroed (-1: a plain copy).
+// Strided copies of `count` field-shaped arrays (1 .. 9) between node arrays (x fastest,
+// unpadded) and the workspace's field storage; comp0 >= 0: array q is component comp0 + q, its
+// pinned slots zeroed.
 template <typename T>
-void copy_field(const fd3d_ctx *c, T *dst, bool dst_fields, const T *src, bool src_fields, int comp, hipStream_t st)
+void copy_arrays(const fd3d_ctx *c, int count, T *const *dst, bool dst_fields, const T *const *src, bool src_fields,
+                 int comp0, hipStream_t st)
 {
     const long nx = c->n[0], ny = c->n[1];
     const long fsy = c->L.rows ? kRows * nx : nx;
-    const long dsy = dst_fields ? fsy : nx, ssy = src_fields ? fsy : nx;
-    const int sx = comp >= 0 ? stag(comp, 0) : 0, sy = comp >= 0 ? stag(comp, 1) : 0, sz = comp >= 0 ? stag(comp, 2) : 0;
-    copy_masked<T><<<1024, 256, 0, st>>>(dst, dsy, dsy * ny, src, ssy, ssy * ny, c->n[0], c->n[1], c->n[2], sx, sy, sz);
+    FieldCopies<T> a;
+    a.dsy = dst_fields ? fsy : nx;
+    a.ssy = src_fields ? fsy : nx;
+    a.dsz = a.dsy * ny;
+    a.ssz = a.ssy * ny;
+    a.nx = c->n[0];
+    a.ny = c->n[1];
+    a.nz = c->n[2];
+    constexpr int V = 16 / (int)sizeof(T);
+    bool wide = nx % V == 0;  // rows of whole 16-byte words, aligned
+    for (int q = 0; q < 9; ++q) {
+        const int p = q < count ? q : 0;
+        FieldCopy<T> &f = a.f[q];
+        f.dst = dst[p];
+        f.src = src[p];
+        f.sx = f.sy = f.sz = 0;
+        if (comp0 >= 0) {
+            f.sx = stag(comp0 + p, 0);
+            f.sy = stag(comp0 + p, 1);
+            f.sz = stag(comp0 + p, 2);
+        }
+        wide = wide && (uintptr_t)f.dst % 16 == 0 && (uintptr_t)f.src % 16 == 0;
+    }
+    const dim3 g(1024, count);
+    if (wide) copy_fields<T, V><<<g, 256, 0, st>>>(a);
+    else copy_fields<T, 1><<<g, 256, 0, st>>>(a);
 }
 
-// Both state copies zeroed, for either element type.
+// The current state zeroed, for either element type.
 void zero_fields_any(fd3d_ctx *c, hipStream_t st);
 
 // Builds the source (tap boxes into inj) and the receiver descriptors and colours, and
@@ -431,7 +456,6 @@ bool fused_supported(const fd3d_ctx *c, int tx, int ty);
 struct GradLayout {
     size_t fstep;   // bytes from one field of a group to the next
     size_t group;   // bytes of a group of nine fields
-    size_t chunk;   // bytes from one field-sized chunk of a group to the next (copies)
     size_t adj;     // 9 fields: A_v, A_s
     size_t acc;     // 8 fields: gl, gm, g_mu_xy, g_mu_xz, g_mu_yz, g_bx, g_by, g_bz
     size_t scr;     // 9 fields: X = C G_s A_s (6, stress layout), Y = G_v A_v / rho_eff (3)
@@ -453,26 +477,11 @@ inline char *seg_slot(char *gws, const GradLayout &GL, int m)
     return gws + GL.seg + (size_t)(m / 3) * GL.group + (size_t)(3 * (m % 3)) * GL.fstep;
 }
 
-// Bytes of a checkpoint group copied to the segment's prev group: the velocity fields (the
-// first three separate arrays), or the whole block of interleaved rows.
-inline size_t prev_copy_bytes(const fd3d_ctx *c, const GradLayout &GL)
-{
-    return c->L.rows ? GL.group : 3 * GL.fstep;
-}
-
 // v^{n-1/2} of segment step m: the previous step's stored v^{n+1/2}, or for m = 0 the
 // velocity fields of the copy of the segment's checkpoint.
 inline char *prev_velocity(char *gws, const GradLayout &GL, int m)
 {
     return m > 0 ? seg_slot(gws, GL, m - 1) : gws + GL.prev;
-}
-
-// The q-th field-sized chunk of the current state (q < 9): field q of separate arrays, or
-// the q-th ninth of the block of interleaved rows.  Checkpoints copy a state chunk by
-// chunk into a group of the same layout.
-template <typename T> char *state_chunk(const fd3d_ctx *c, const Grid<T> &G, int q)
-{
-    return c->L.rows ? (char *)G.f[0] + (size_t)q * c->L.chunk : (char *)G.f[q];
 }
 
 // The nt-step forward of a context (checkpoints into gws with GL); float and double.
@@ -572,12 +581,22 @@ template <typename T> void launch_gb_initial(const Grid<T> &G, const AdjGrid<T> 
     gb_initial_velocity<T><<<grd, blk, 0, st>>>(G, v0(0), v0(1), v0(2), y(0), y(1), y(2), A.gb[0], A.gb[1], A.gb[2]);
 }
 
-// Zero the adjoint state, accumulators and intermediate fields, and the segment slots
-// (whose samples at the pinned staggered positions are never stored and must read 0).
-template <typename T> void zero_grad_fields(char *gws, const GradLayout &GL, hipStream_t st)
+// Zero the adjoint state, accumulators and intermediate fields, and the segment's stored
+// velocities at the pinned staggered positions, which are never stored and must read 0.
+template <typename T> void zero_grad_fields(const Grid<T> &G, char *gws, const GradLayout &GL, hipStream_t st)
 {
     fill_zero<T><<<2048, 256, 0, st>>>((T *)(gws + GL.adj), (long)((GL.ckpt - GL.adj) / sizeof(T)));
-    fill_zero<T><<<2048, 256, 0, st>>>((T *)(gws + GL.seg), (long)((GL.res - GL.seg) / sizeof(T)));
+    for (int m0 = 0; m0 < GL.k; m0 += 3 * 4096) {  // whole groups, at most the largest grid of blocks
+        const int slots = std::min(GL.k - m0, 3 * 4096);
+        zero_pinned<T><<<dim3(16, 3 * slots), 256, 0, st>>>(seg_slot(gws, GL, m0), GL.group, GL.fstep, G.nx, G.ny, G.nz,
+                                                            G.sy, G.sz);
+    }
+}
+
+// Copies the nine fields of a group (of the state, or a checkpoint) with the pads between them.
+inline void copy_group(const fd3d_ctx *c, char *dst, const char *src, hipStream_t st)
+{
+    copy_block<<<2048, 256, 0, st>>>((float4 *)dst, (const float4 *)src, (long)(c->L.group / 16));
 }
 
 // Validates a caller's gradient workspace for checkpoints every k steps.

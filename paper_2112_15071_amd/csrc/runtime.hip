@@ -51,7 +51,6 @@ Layout make_layout(int nx, int ny, int nz, int tsize, int max_rec, bool rows, bo
     const size_t stride = round_up(L.field_bytes, 4096) + 1024;
     L.fstep = rows ? (size_t)nx * tsize : stride;
     L.group = rows ? round_up(kRows * L.field_bytes, 4096) + 1024 : NFIELD * stride;
-    L.chunk = rows ? L.field_bytes : stride;
     for (int b = 0; b < 2; ++b) {
         for (int f = 0; f < NFIELD; ++f) L.field[b][f] = off + f * L.fstep;
         off += L.group;
@@ -197,7 +196,7 @@ template <typename T> int model_check(fd3d_ctx *c, hipStream_t st)
     double *out = (double *)(c->ws + c->L.stats);
     model_stats<T><<<kReduceBlocks, kReduceThreads, 0, st>>>((const T *)c->lam, (const T *)c->mu,
                                                             (const T *)c->rho, N, part);
-    stats_final<<<1, kReduceThreads, 0, st>>>(part, kReduceBlocks, out);
+    stats_final<<<1, kStats * 64, 0, st>>>(part, kReduceBlocks, out);
     HIP_TRY(hipGetLastError());
     double s[kStats];
     HIP_TRY(hipMemcpyAsync(s, out, sizeof s, hipMemcpyDeviceToHost, st));
@@ -228,9 +227,10 @@ template <typename T> void copy_model(fd3d_ctx *c, hipStream_t st)
     if (!c->L.model) return;
     T *m = (T *)(c->ws + c->L.model);
     fill_zero<T><<<2048, 256, 0, st>>>(m, (long)(c->L.group / sizeof(T)));
-    const void *src[3] = {c->lam, c->mu, c->rho};
-    for (int q = 0; q < 3; ++q)
-        copy_field<T>(c, (T *)((char *)m + q * c->L.fstep), true, (const T *)src[q], false, -1, st);
+    const T *src[3] = {(const T *)c->lam, (const T *)c->mu, (const T *)c->rho};
+    T *dst[3];
+    for (int q = 0; q < 3; ++q) dst[q] = (T *)((char *)m + q * c->L.fstep);
+    copy_arrays<T>(c, 3, dst, true, src, false, -1, st);
 }
 
 // The source's tap boxes into inj and its coefficients into the host staging buffer
@@ -285,7 +285,7 @@ template <typename T> int build_source(fd3d_ctx *c, const fd3d_source *src, Inje
 template <typename T> int set_state_impl(fd3d_ctx *c, const void *const fields[9], hipStream_t st)
 {
     const Grid<T> G = make_grid<T>(c);
-    for (int f = 0; f < NFIELD; ++f) copy_field<T>(c, G.f[f], true, (const T *)fields[f], false, f, st);
+    copy_arrays<T>(c, NFIELD, G.f, true, (const T *const *)fields, false, 0, st);
     HIP_TRY(hipGetLastError());
     return FD3D_OK;
 }
@@ -512,12 +512,12 @@ int create_ctx(fd3d_ctx **out, int nx, int ny, int nz, const void *lam, const vo
     if (c->tsize == 8) {
         rc = model_check<double>(c, st);
         if (!rc) rc = upload_profiles<double>(c, st);
-        if (!rc) zero_fields<double>(c, st);
+        if (!rc) fill_zero<double><<<2048, 256, 0, st>>>((double *)c->ws, (long)(2 * c->L.group / 8));
         if (!rc) copy_model<double>(c, st);
     } else {
         rc = model_check<float>(c, st);
         if (!rc) rc = upload_profiles<float>(c, st);
-        if (!rc) zero_fields<float>(c, st);
+        if (!rc) fill_zero<float><<<2048, 256, 0, st>>>((float *)c->ws, (long)(2 * c->L.group / 4));
         if (!rc) copy_model<float>(c, st);
     }
     if (!rc && hipGetLastError() != hipSuccess) rc = fail(FD3D_EHIP, "launch failed in fd3d_create");
@@ -547,14 +547,15 @@ int fd3d_get_state(fd3d_ctx *ctx, void *const fields[9], void *hip_stream)
     for (int f = 0; f < NFIELD; ++f)
         if (!fields[f]) return fail(FD3D_EINVAL, "field pointer is NULL");
     hipStream_t st = (hipStream_t)hip_stream;
-    for (int f = 0; f < NFIELD; ++f) {
-        const char *a = ctx->ws + ctx->L.field[ctx->cur][f];
-        if (!ctx->L.rows)
-            HIP_TRY(hipMemcpyAsync(fields[f], a, ctx->L.field_bytes, hipMemcpyDeviceToDevice, st));
-        else if (ctx->tsize == 8)
-            copy_field<double>(ctx, (double *)fields[f], false, (const double *)a, true, -1, st);
-        else
-            copy_field<float>(ctx, (float *)fields[f], false, (const float *)a, true, -1, st);
+    const char *a[NFIELD];
+    for (int f = 0; f < NFIELD; ++f) a[f] = ctx->ws + ctx->L.field[ctx->cur][f];
+    if (!ctx->L.rows) {
+        for (int f = 0; f < NFIELD; ++f)
+            HIP_TRY(hipMemcpyAsync(fields[f], a[f], ctx->L.field_bytes, hipMemcpyDeviceToDevice, st));
+    } else if (ctx->tsize == 8) {
+        copy_arrays<double>(ctx, NFIELD, (double *const *)fields, false, (const double *const *)a, true, -1, st);
+    } else {
+        copy_arrays<float>(ctx, NFIELD, (float *const *)fields, false, (const float *const *)a, true, -1, st);
     }
     HIP_TRY(hipGetLastError());
     return FD3D_OK;
