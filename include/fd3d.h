@@ -293,8 +293,10 @@ int fd3d_batch_set_kernel(fd3d_batch *b, int tile_x, int tile_y, int workgroups)
  * otherwise.  fd3d_batch_set_kernel sets one shape. */
 int fd3d_batch_set_tiles(fd3d_batch *b, int tile_x, int tile_y, int tile2_x, int tile2_y, int workgroups);
 
-/* Order of the batched forward.  group_bytes = 0 (default): lockstep, every launch covers
- * every shot and all shots advance one step at a time.  group_bytes > 0: cache-blocked
+/* Order of the batched forward.  Until a schedule, tile shapes or the tuner are selected, the
+ * library forms cache-blocked groups by itself (see below; lockstep where all shots fit the
+ * last-level cache together).  group_bytes = 0: lockstep, every launch covers every shot and
+ * all shots advance one step at a time.  group_bytes > 0: cache-blocked
  * groups -- runs of consecutive shots (in batch order) whose working sets (9 fields and
  * 3 model arrays each, 12 x cells x sizeof(T) bytes per shot) add up to at most
  * group_bytes (a group holds at least one shot); each group runs all nt steps, one launch
@@ -305,7 +307,8 @@ int fd3d_batch_set_tiles(fd3d_batch *b, int tile_x, int tile_y, int tile2_x, int
  * groups use the batch's shapes.  Results per shot are the same in both orders. */
 int fd3d_batch_set_schedule(fd3d_batch *b, size_t group_bytes);
 
-/* Times `steps` batched steps (sources and receivers off, one warm-up run each) for
+/* Times `steps` batched steps past the first (sources and receivers off, one warm-up run
+ * each) with the library's own choice (best keeps the values set before if it wins), for
  * every supported tile shape and pair of shapes in lockstep, with the persistent grid
  * and with one workgroup per tile, then the cache-blocked schedule with group budgets of
  * 96, 128, 192, 256 and 384 MiB; keeps the fastest for later batch calls and writes it to best =

@@ -314,8 +314,8 @@ int fd3d_autotune(fd3d_ctx *ctx, int steps, fd3d_kernel *best, double *best_ms, 
     const fd3d_kernel keep = {ctx->variant, ctx->tile_x, ctx->tile_y, ctx->zchunk};
     const bool keep_auto = ctx->auto_kernel;
     ctx->auto_kernel = false;
-    fd3d_kernel win = keep;
-    double win_ms = 1e300;
+    fd3d_kernel win = keep, win_tile = keep;  // the best of all, and of the tile sweeps
+    double win_ms = 1e300, tile_ms = 1e300;
     hipEvent_t e0 = nullptr, e1 = nullptr;
     if (hipEventCreate(&e0) != hipSuccess || hipEventCreate(&e1) != hipSuccess) {
         if (e0) (void)hipEventDestroy(e0);
@@ -360,9 +360,17 @@ int fd3d_autotune(fd3d_ctx *ctx, int steps, fd3d_kernel *best, double *best_ms, 
                 win_ms = ms;
                 win = fd3d_kernel{sh[0], sh[1], sh[2], zc};
             }
+            if (sh[0] == FD3D_KERNEL_TILE && ms < tile_ms) {
+                tile_ms = ms;
+                win_tile = fd3d_kernel{sh[0], sh[1], sh[2], zc};
+            }
         }
         if (rc) break;
     }
+    // the cell kernels have no tile: the context keeps the best sweep's beside them, which
+    // batches use where they run sweeps
+    if (win.variant == FD3D_KERNEL_CELL && tile_ms < 1e300)
+        win = fd3d_kernel{FD3D_KERNEL_CELL, win_tile.tile_x, win_tile.tile_y, win_tile.zchunk};
     ctx->nt = nt_save;
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);

@@ -134,3 +134,30 @@ def test_batch(select):
     batch.close()
     for s in sims:
         s.close()
+
+
+@pytest.mark.parametrize("tune", [False, True])
+def test_batch_default_groups(tune):
+    """Shots that exceed the cache together run in groups when no schedule is selected (one shot
+    alone, two rows shots, one sweep of a large shot), untuned and tuned, and equal the lockstep."""
+    from paper_2112_15071_amd import Simulator
+    from paper_2112_15071_amd.batch import BatchSimulator
+
+    shapes = [(256, 200, 110), (120, 110, 100), (128, 96, 80), (130, 128, 120)]  # 258, 60, 45, 92 MiB
+    parts = [setup(s, seed=50 + k) for k, s in enumerate(shapes)]
+    sims = [Simulator(*m, H, DT, NT, sponge=3) for m, _ in parts]
+    shots = [sh for _, sh in parts]
+    batch = BatchSimulator(sims)
+    if tune:
+        batch.autotune(1, cache=False)
+    out = [[t.clone() for t in batch.forward(shots, use_graph=graph)] for graph in (False, True, True)]
+    batch.close()
+    batch = BatchSimulator(sims)
+    batch.set_kernel(64, 8)
+    batch.set_schedule(0)
+    ref = [t.clone() for t in batch.forward(shots, use_graph=False)]
+    for r in out:
+        same([r, ref])
+    batch.close()
+    for s in sims:
+        s.close()
