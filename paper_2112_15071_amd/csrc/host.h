@@ -362,7 +362,7 @@ inline Kern kernels_of(const fd3d_ctx *c, int arrays)
 }
 
 // Work of a row launch over a grid.  Blocks as wide as the rows, of the width that leaves the
-// fewest lanes idle (the widest of equals; 149 x 101 x 87: 32.8 us a step with 64 columns, 35.6
+// fewest lanes idle (the widest of equals; 149 x 101 x 87: 32.2 us a step with 64 columns, 35.6
 // with 256).  Grids whose planes are small are cut into 8 slabs of planes, one per XCD: the few
 // planes that neighbouring cells share stay in its 4 MiB L2 (64^3: 10.3 us against 10.3 in 8
 // strips and 14.1 in 4).  Larger planes are cut into strips of at most 32 rows instead (256 x 256

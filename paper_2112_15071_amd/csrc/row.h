@@ -16,7 +16,7 @@
 //   grid             rows    tile sweep   vel_cell / stress_cell
 //   32^3              6.9       14.5        15.1
 //   64^3             10.3       19.5        19.4
-//   149 x 101 x 87   32.8       40.7        73.9
+//   149 x 101 x 87   32.2       40.7        73.9
 //   128^3            35.9       45.7        69.8   (7.0 TB/s of 120 B per cell)
 //   192 x 192 x 128  88.7       94.3
 //   256^3           448        364
@@ -80,8 +80,9 @@ __device__ __forceinline__ RowPos row_pos(const RowMap &rm, int nz, int x, int y
 
 // Byte offsets of a wave's samples in the window of its plane: column i + d (per lane), row
 // j + a and plane k + c (uniform).  Columns outside the grid get kOOB, rows and planes kSkip
-// (see Window): an offset with any of them is out of range, or wraps into the window only for
-// lanes past the last column, whose stores are dropped.
+// (see Window): an offset with any of them is out of range.  Lanes past the last column leave at
+// once (they may wrap into the window): their loads took as long as the others' (149 x 101 x 87:
+// 34.0 us a step with them, 32.2 without; 330 x 70 x 60: 33.1 and 32.3; no change at 128^3).
 template <typename T> struct RowOffsets {
     Window w;
     int i, j, k, nx, ny, nz;
@@ -216,9 +217,8 @@ template <typename T> struct Damping {
 
     __device__ __forceinline__ Damping(const Grid<T> &G, const RowPos &p)
     {
-        const int i = p.i < G.nx ? p.i : G.nx - 1;
-        xi = G.g[0][0][i];
-        xh = G.g[0][1][i];
+        xi = G.g[0][0][p.i];
+        xh = G.g[0][1][p.i];
         yi = sload(G.g[1][0], p.j);
         yh = sload(G.g[1][1], p.j);
         zi = sload(G.g[2][0], p.k);
@@ -239,7 +239,7 @@ __device__ __forceinline__ void vel_row_body(const Grid<T> &G, const Inject<T> &
                                              const TileIO<T> &io)
 {
     constexpr bool born = MODE == kBornV, adj = MODE == kAdjA;
-    if (p.k >= G.nz || p.j >= G.ny) return;  // wave-uniform
+    if (p.k >= G.nz || p.j >= G.ny || p.i >= G.nx) return;
     const RowOffsets<T> o(G, p);
     const unsigned own = o(0, 0, 0);
     const SigmaTaps<T> t = load_sigma<FS, T>(G.f + SXX, o);
@@ -311,7 +311,7 @@ __device__ __forceinline__ void stress_row_body(const Grid<T> &G, const Inject<T
                                                 const TileIO<T> &io)
 {
     constexpr bool born = MODE == kBornS, adjm = MODE == kAdjM, adjb = MODE == kAdjB;
-    if (p.k >= G.nz || p.j >= G.ny) return;  // wave-uniform
+    if (p.k >= G.nz || p.j >= G.ny || p.i >= G.nx) return;
     const RowOffsets<T> o(G, p);
     const unsigned own = o(0, 0, 0);
     const VelTaps<T> t = load_velocity<T>(G.f + VX, o);
