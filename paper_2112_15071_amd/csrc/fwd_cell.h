@@ -1,8 +1,9 @@
 // One-thread-per-cell forward passes (velocity, stress) and receiver sampling.
 //
 // Every neighbour is read straight from global memory with a bounds test; this
-// is the simplest complete form of the passes and serves small grids, the FP64
-// mode and the free-surface top planes.
+// is the simplest complete form of the passes.  The cell variant runs the row
+// kernels (row.h) and falls back to these where a few planes of a field exceed
+// the row kernels' buffer window.
 #pragma once
 
 #include "common.h"

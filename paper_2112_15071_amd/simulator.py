@@ -194,9 +194,11 @@ class Simulator:
     _VARIANTS = {"cell": 0, "tile": 1, "fused": 2}
 
     def set_kernel(self, variant: str = "tile", tile_y: int = 8, zchunk: int = 32, tile_x: int = 64) -> None:
-        """Select the step-loop kernels: "cell" (one thread per cell), "tile" (LDS halo
-        planes + register z sweep over tile_x x tile_y columns, zchunk planes) or "fused"
-        (velocity and stress of a step in one sweep, tile_x = 64)."""
+        """Select the step-loop kernels: "cell" (one thread per cell, a row of cells per
+        wave), "tile" (LDS halo planes + register z sweep over tile_x x tile_y columns,
+        zchunk planes) or "fused" (velocity and stress of a step in one sweep, tile_x = 64).
+        Until one is selected or tuned, each operation takes "cell" while its arrays stay
+        in the last-level cache and "tile" sweeps otherwise."""
         k = _abi.fd3d_kernel()
         k.variant = self._VARIANTS[variant]
         k.tile_x, k.tile_y, k.zchunk = int(tile_x), int(tile_y), int(zchunk)
