@@ -479,21 +479,29 @@ __global__ void __launch_bounds__(256) stress_row_io(Grid<T> G, Inject<T> src, i
 // strip, plane by plane), cut into 8 equal runs, one per XCD.  Block b takes entry b / 8 of the
 // run of XCD b mod 8 (the passes that walk backwards count from the last).  Runs rather than 8
 // slabs of every shot: four shots of 96 x 80 x 72, forward step 56.4 us
-// against 57.6; 40 x 50 x 60 by six: 30.3 against 31.3.
+// against 57.6; 40 x 50 x 60 by six: 30.3 against 31.3 (both before the search below).
+// A block finds its shot by a binary search through the scalar cache: a table of the bases in
+// LDS, as the persistent tile launches keep one, costs every block a load, a barrier and a scan
+// before its first sample (six shots of 96 x 80 x 72 80.2 us a step with it, 76.1 without; one
+// of 149 x 101 x 87 37.2 and 34.1; one of 128^3 41.3 and 39.4).
 struct ShotRows {  // a shot's blocks, and the first of them in the list
     RowMap rm;
     int base;
 };
 
 template <typename T>
-__device__ __forceinline__ const ShotFwd<T> &row_shot(const ShotFwd<T> *shots, const ShotRows *rows, int *s_base, int nshot,
-                                                      int total, bool reverse, RowPos &p)
+__device__ __forceinline__ const ShotFwd<T> &row_shot(const ShotFwd<T> *shots, const ShotRows *rows, int nshot, int total,
+                                                      bool reverse, RowPos &p)
 {
-    load_bases(s_base, &rows[0].base, base_stride<ShotRows>(), nshot);
     const int per = (total + 7) / 8, q = (int)blockIdx.x >> 3;
     const int at = ((int)blockIdx.x & 7) * per + (reverse ? per - 1 - q : q);
     const int l = at < total ? at : total - 1;  // past the last block: no work (below)
-    const int s = shot_of(s_base, nshot, l);
+    int s = 0;
+    for (int e = nshot; e - s > 1;) {
+        const int m = (s + e) >> 1;
+        if (sload(&rows[m].base, 0) <= l) s = m;
+        else e = m;
+    }
     const ShotFwd<T> &d = shots[s];
     const RowMap rm = rows[s].rm;
     const int b = l - rows[s].base, strip = rm.ns > 1 ? b / (rm.tiles() * rm.np) : 0, r = b - strip * rm.tiles() * rm.np;
@@ -506,9 +514,8 @@ template <typename T, bool FS, int MODE, bool VAC>
 __global__ void __launch_bounds__(256) vel_row_multi(const ShotFwd<T> *__restrict__ shots,
                                                      const ShotRows *__restrict__ rows, int nshot, int total, int n)
 {
-    __shared__ int s_base[kMaxShots];
     RowPos p;
-    const ShotFwd<T> &d = row_shot(shots, rows, s_base, nshot, total, vel_sweeps_up<MODE>(), p);
+    const ShotFwd<T> &d = row_shot(shots, rows, nshot, total, vel_sweeps_up<MODE>(), p);
     const Grid<T> G = d.G;
     const Inject<T> src = d.src;
     const TileIO<T> io = d.io;
@@ -520,13 +527,13 @@ __global__ void __launch_bounds__(256) stress_row_multi(const ShotFwd<T> *__rest
                                                         const ShotRows *__restrict__ rows, int nshot, int total, int n,
                                                         RecMulti<T> rec)
 {
-    __shared__ int s_base[kMaxShots];
     if ((int)blockIdx.x >= rec.wgs) {
+        __shared__ int s_base[kMaxShots];
         sample_batch_receivers(rec, s_base, n);
         return;
     }
     RowPos p;
-    const ShotFwd<T> &d = row_shot(shots, rows, s_base, nshot, total, stress_sweeps_up<MODE>(), p);
+    const ShotFwd<T> &d = row_shot(shots, rows, nshot, total, stress_sweeps_up<MODE>(), p);
     const Grid<T> G = d.G;
     const Inject<T> src = d.src;
     const TileIO<T> io = d.io;
