@@ -308,13 +308,13 @@ int fd3d_batch_set_tiles(fd3d_batch *b, int tile_x, int tile_y, int tile2_x, int
 int fd3d_batch_set_schedule(fd3d_batch *b, size_t group_bytes);
 
 /* Times `steps` batched steps past the first (sources and receivers off, one warm-up run
- * each) with the library's own choice (best keeps the values set before if it wins), for
- * every supported tile shape and pair of shapes in lockstep, with the persistent grid
- * and with one workgroup per tile, then the cache-blocked schedule with group budgets of
- * 96, 128, 192, 256 and 384 MiB; keeps the fastest for later batch calls and writes it to best =
- * {tile_x, tile_y, tile2_x, tile2_y, workgroups (0 = persistent), group MiB (0 =
- * lockstep)} and its ms per step to *best_ms (each when non-NULL).  Every shot's forward
- * state is zeroed afterwards.  Synchronises the stream. */
+ * each) for every supported tile shape and pair of shapes in lockstep, with the persistent
+ * grid and with one workgroup per tile, then the library's own choice (reported as group
+ * 230) and the cache-blocked schedule with group budgets of 96, 128, 192, 256 and 384 MiB;
+ * keeps the fastest for later batch calls and writes it to best = {tile_x, tile_y, tile2_x,
+ * tile2_y, workgroups (0 = persistent), group MiB (0 = lockstep)} and its ms per step to
+ * *best_ms (each when non-NULL).  Every shot's forward state is zeroed afterwards.
+ * Synchronises the stream. */
 int fd3d_batch_autotune(fd3d_batch *b, int steps, int best[6], double *best_ms, void *hip_stream);
 
 /* srcs[nshot] (or NULL), nrec[nshot], rec_pos[nshot] (host double[nrec][3] each),

@@ -194,9 +194,10 @@ template <typename C> long tile_columns(const BatchGroup &g, int ns, C &&shot)
 
 // Whether the launches over these shots run the row kernels: when no shot has a tile or fused
 // kernel selected and the arrays of all of them (`arrays` per shot) together stay in the
-// Infinity Cache (kernels_of).  In lockstep, us per step, rows / tile sweeps: six shots of 40 x 50
-// x 60 30.3 / 78.3 (31.3 with the depth of one round), three of 40^3 13.2, four of 96 x 80 x 72
-// (106 MB) 56.4 / 81.8.
+// Infinity Cache (kernels_of).  In lockstep, us per step, rows / best tile sweep (with the depth
+// of one round), forward and gradient: six shots of 40 x 50 x 60 30.0 / 31.6 and 112.9 / 133.6,
+// eight of 64^3 46.7 / 50.6 and 208.7 / 212.1, four of 96 x 80 x 72 (106 MB) 54.1 / 54.3 and 244.2
+// / 244.3, four of 128 x 96 x 80 (189 MB) 71.5 / 79.7 and 342.3 / 348.2.
 bool batch_rows(const fd3d_ctx *const *ctx, int ns, int arrays)
 {
     double bytes = 0.0;
@@ -351,8 +352,8 @@ void make_groups(fd3d_batch *b)
     for (int s = 0; s < b->nshot; ++s) b->order[s] = s;
     BatchGroup all = whole_batch(b);
     // with neither schedule nor tile shapes selected, groups that stay in the Infinity Cache
-    // (one shot per group where a shot alone exceeds it): three shots of 128^3 118.6 us per step
-    // against 134 in lockstep, two each of 128^3, 192 x 192 x 128 and 256 x 256 x 128 592 against 752
+    // (one shot per group where a shot alone exceeds it): three shots of 128^3 118.4 us per step
+    // against 134 in lockstep, two each of 128^3, 192 x 192 x 128 and 256 x 256 x 128 584 against 752
     const size_t budget = b->sched_set || b->tiles_set ? b->group_bytes : (size_t)kRowBytes32;
     if (budget == 0) {
         all.cols = tile_columns(all, b->nshot, [&](int q) { return b->ctx[q]; });
@@ -867,7 +868,7 @@ int fd3d_batch_autotune(fd3d_batch *b, int steps, int best[6], double *best_ms, 
     const int nt_save = b->nt;
     const size_t keep_group = b->group_bytes;
     const bool keep_set = b->tiles_set, keep_sched = b->sched_set;
-    bool win_set = keep_set, win_sched = true;
+    bool win_set = keep_set;
     const int keep[5] = {b->tile_x, b->tile_y, b->tile2_x, b->tile2_y, b->wgs_req};
     int win[5] = {keep[0], keep[1], keep[2], keep[3], keep[4]};
     int win_mib = 0;
@@ -901,16 +902,8 @@ int fd3d_batch_autotune(fd3d_batch *b, int steps, int best[6], double *best_ms, 
         if (!rc) run(1, t);
         if (!rc) run(1, t);
         if (!rc) run(steps + 1, ms);
-        ms -= t;
+        ms = ms > t ? ms - t : ms * steps / (steps + 1);
     };
-    // the batch's own choice: row kernels, groups that stay in the cache
-    b->tiles_set = b->sched_set = false;
-    {
-        float ms = 0.0f;
-        time_it(ms);
-        win_ms = rc ? win_ms : ms;
-        win_set = win_sched = false;
-    }
     b->tiles_set = b->sched_set = true;
     for (const auto &sh : shapes) {
         if (rc) break;
@@ -939,7 +932,7 @@ int fd3d_batch_autotune(fd3d_batch *b, int steps, int best[6], double *best_ms, 
             if (rc) break;
             if (ms < win_ms) {
                 win_ms = ms;
-                win_set = win_sched = true;
+                win_set = true;
                 win[0] = b->tile_x;
                 win[1] = b->tile_y;
                 win[2] = b->tile2_x;
@@ -949,14 +942,25 @@ int fd3d_batch_autotune(fd3d_batch *b, int steps, int best[6], double *best_ms, 
         }
         if (rc) break;
     }
-    // the schedule, with the winning shapes for the launches that use the batch's shapes
+    // the schedule, with the winning shapes for the launches that use the batch's shapes: the
+    // batch's own choice (row kernels, groups that stay in the cache), then the budgets
     if (!rc) {
         b->tile_x = win[0];
         b->tile_y = win[1];
         b->tile2_x = win[2];
         b->tile2_y = win[3];
         b->wgs_req = win[4];
+        b->tiles_set = b->sched_set = false;
+        float own = 0.0f;
+        time_it(own);
+        if (!rc && own < win_ms) {
+            win_ms = own;
+            win_set = false;
+            win_mib = (int)(kRowBytes32 / (1 << 20));
+        }
+        b->tiles_set = b->sched_set = true;
         for (int mib : budgets) {
+            if (rc) break;
             b->group_bytes = (size_t)mib << 20;
             float ms = 0.0f;
             time_it(ms);
@@ -964,7 +968,7 @@ int fd3d_batch_autotune(fd3d_batch *b, int steps, int best[6], double *best_ms, 
             if (ms < win_ms) {
                 win_ms = ms;
                 win_mib = mib;
-                win_set = win_sched = true;
+                win_set = true;
             }
         }
     }
@@ -978,7 +982,7 @@ int fd3d_batch_autotune(fd3d_batch *b, int steps, int best[6], double *best_ms, 
     b->tile2_y = use[3];
     b->wgs_req = use[4];
     b->tiles_set = rc ? keep_set : win_set;
-    b->sched_set = rc ? keep_sched : win_sched;
+    b->sched_set = rc ? keep_sched : true;
     b->group_bytes = rc ? keep_group : (size_t)win_mib << 20;
     if (rc) return rc;
     for (fd3d_ctx *c : b->ctx) zero_fields_any(c, st);
