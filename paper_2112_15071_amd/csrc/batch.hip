@@ -219,7 +219,7 @@ void launch_rows_multi(const BatchGroup &gr, const ShotFwd<T> *d, int n, int pas
 {
     const int S = gr.ns, W = gr.rtiles, g = (W + 7) / 8 * 8;
     const RecMulti<T> rec{r, S, (r && pass == kPassStress) ? gr.recs : 0, nt, g};
-    const int gs = g + rec_blocks(rec, 256);
+    const int gs = g + (rec_blocks(rec, 256) + 7) / 8 * 8;
     if constexpr (!FS) {
         if (gr.vac && pass == kPassVel) {
             vel_row_multi<T, false, kFwd, true><<<g, 256, 0, st>>>(d, gr.rows, S, W, n);

@@ -211,8 +211,8 @@ __device__ __forceinline__ int rec_shot(const int *s_base, int nshot, int q)
     return s;
 }
 
-// Receiver sampling of a batch carried by a persistent launch of wgs workgroups: the
-// workgroups past the first wgs take the total work items of the flat list.
+// Receiver sampling of a batch carried by a launch of wgs workgroups besides: the
+// workgroups past (row launches: before) those take the total work items of the flat list.
 template <typename T> struct RecMulti {
     const ShotRec<T> *shots;
     int nshot, total, nt, wgs;
@@ -220,15 +220,21 @@ template <typename T> struct RecMulti {
 
 template <typename T> inline int rec_blocks(const RecMulti<T> &r, int nt) { return (r.total + nt - 1) / nt; }
 
-// Body of one such workgroup (block-uniform; s_base: LDS scratch of kMaxShots ints).
-template <typename T> __device__ __forceinline__ void sample_batch_receivers(const RecMulti<T> &r, int *s_base, int n)
+// Body of the block-th such workgroup (block-uniform; s_base: LDS scratch of kMaxShots ints).
+template <typename T>
+__device__ __forceinline__ void sample_batch_receivers(const RecMulti<T> &r, int *s_base, int n, int block)
 {
     for (int t = threadIdx.x; t < r.nshot; t += blockDim.x) s_base[t] = r.shots[t].base;
     __syncthreads();
-    const int q = ((int)blockIdx.x - r.wgs) * (int)blockDim.x + (int)threadIdx.x;
+    const int q = block * (int)blockDim.x + (int)threadIdx.x;
     if (q >= r.total) return;
     const int s = rec_shot(s_base, r.nshot, q);
     sample_shot_receiver(r.shots[s], q - r.shots[s].base, r.nt, n);
+}
+
+template <typename T> __device__ __forceinline__ void sample_batch_receivers(const RecMulti<T> &r, int *s_base, int n)
+{
+    sample_batch_receivers(r, s_base, n, (int)blockIdx.x - r.wgs);
 }
 
 } // namespace fd3d

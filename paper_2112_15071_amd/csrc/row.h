@@ -424,30 +424,33 @@ __device__ __forceinline__ void stress_row_body(const Grid<T> &G, const Inject<T
 
 // ---------------------------------------------------------------------------------
 // Single-grid launches: grid (8, rm.tiles(), rm.planes()), which the hardware deals round robin
-// over the 8 XCDs along x; blocks past rm.planes() sample receivers.  The stress pass walks the
-// planes backwards, from where the velocity pass ended.
+// over the 8 XCDs along x.  The stress pass walks the planes backwards, from where the velocity
+// pass ended.  Its blocks before the last rm.planes() along z sample receivers: a receiver takes
+// two dependent loads from the far side of the L2s, and sampled by the last blocks it outlasted
+// the cells (us a step, last / first: 64^3, 16 receivers 13.0 / 11.8; 149 x 101 x 87, 256
+// receivers 35.2 / 31.3; 128^3, 256 receivers 41.1 / 37.4).
 template <typename T, bool FS, int MODE, bool VAC>
 __global__ void __launch_bounds__(256) vel_row(Grid<T> G, Inject<T> src, int n, RowMap rm)
 {
     vel_row_body<T, FS, MODE, VAC>(G, src, n, row_pos(rm, G.nz, blockIdx.x, blockIdx.y, blockIdx.z, false), TileIO<T>{});
 }
 
-// Receiver work item of this thread in the blocks past the planes.
-__device__ __forceinline__ int row_receiver(const RowMap &rm)
+// Receiver work item of this thread in the blocks before the planes.
+__device__ __forceinline__ int row_receiver()
 {
-    return ((((int)blockIdx.z - rm.planes()) * (int)gridDim.y + (int)blockIdx.y) * 8 + (int)blockIdx.x) * 256 +
-           (int)threadIdx.x;
+    return (((int)blockIdx.z * (int)gridDim.y + (int)blockIdx.y) * 8 + (int)blockIdx.x) * 256 + (int)threadIdx.x;
 }
 
 template <typename T, bool FS, bool VAC>
 __global__ void __launch_bounds__(256) stress_row(Grid<T> G, Inject<T> src, int n, RowMap rm, RecJob<T> rec)
 {
-    if ((int)blockIdx.z >= rm.planes()) {
-        const int q = row_receiver(rm);
+    const int z = (int)blockIdx.z - ((int)gridDim.z - rm.planes());
+    if (z < 0) {
+        const int q = row_receiver();
         if (q < rec.nq) sample_receiver(rec, q, n);
         return;
     }
-    stress_row_body<T, FS, kFwd, VAC>(G, src, n, row_pos(rm, G.nz, blockIdx.x, blockIdx.y, blockIdx.z, true), TileIO<T>{});
+    stress_row_body<T, FS, kFwd, VAC>(G, src, n, row_pos(rm, G.nz, blockIdx.x, blockIdx.y, z, true), TileIO<T>{});
 }
 
 // Adjoint and Born passes.
@@ -463,14 +466,15 @@ template <typename T, int MODE>
 __global__ void __launch_bounds__(256) stress_row_io(Grid<T> G, Inject<T> src, int n, RowMap rm, TileIO<T> io, RecJob<T> rec,
                                                      RecJob<T> prec)
 {
-    if ((int)blockIdx.z >= rm.planes()) {
-        const int q = row_receiver(rm);
+    const int z = (int)blockIdx.z - ((int)gridDim.z - rm.planes());
+    if (z < 0) {
+        const int q = row_receiver();
         if (q < rec.nq) sample_receiver(rec, q, n);
         else if (q - rec.nq < prec.nq) sample_receiver(prec, q - rec.nq, n);
         return;
     }
     constexpr bool up = stress_sweeps_up<MODE>();
-    const RowPos p = row_pos(rm, G.nz, blockIdx.x, blockIdx.y, blockIdx.z, up);
+    const RowPos p = row_pos(rm, G.nz, blockIdx.x, blockIdx.y, z, up);
     stress_row_body<T, false, MODE, false>(G, src, n, p, io);
 }
 
@@ -491,10 +495,10 @@ struct ShotRows {  // a shot's blocks, and the first of them in the list
 
 template <typename T>
 __device__ __forceinline__ const ShotFwd<T> &row_shot(const ShotFwd<T> *shots, const ShotRows *rows, int nshot, int total,
-                                                      bool reverse, RowPos &p)
+                                                      int block, bool reverse, RowPos &p)
 {
-    const int per = (total + 7) / 8, q = (int)blockIdx.x >> 3;
-    const int at = ((int)blockIdx.x & 7) * per + (reverse ? per - 1 - q : q);
+    const int per = (total + 7) / 8, q = block >> 3;
+    const int at = (block & 7) * per + (reverse ? per - 1 - q : q);
     const int l = at < total ? at : total - 1;  // past the last block: no work (below)
     int s = 0;
     for (int e = nshot; e - s > 1;) {
@@ -515,7 +519,7 @@ __global__ void __launch_bounds__(256) vel_row_multi(const ShotFwd<T> *__restric
                                                      const ShotRows *__restrict__ rows, int nshot, int total, int n)
 {
     RowPos p;
-    const ShotFwd<T> &d = row_shot(shots, rows, nshot, total, vel_sweeps_up<MODE>(), p);
+    const ShotFwd<T> &d = row_shot(shots, rows, nshot, total, (int)blockIdx.x, vel_sweeps_up<MODE>(), p);
     const Grid<T> G = d.G;
     const Inject<T> src = d.src;
     const TileIO<T> io = d.io;
@@ -527,13 +531,14 @@ __global__ void __launch_bounds__(256) stress_row_multi(const ShotFwd<T> *__rest
                                                         const ShotRows *__restrict__ rows, int nshot, int total, int n,
                                                         RecMulti<T> rec)
 {
-    if ((int)blockIdx.x >= rec.wgs) {
+    const int block = (int)blockIdx.x - ((int)gridDim.x - rec.wgs);  // receivers first (a multiple of 8 blocks)
+    if (block < 0) {
         __shared__ int s_base[kMaxShots];
-        sample_batch_receivers(rec, s_base, n);
+        sample_batch_receivers(rec, s_base, n, (int)blockIdx.x);
         return;
     }
     RowPos p;
-    const ShotFwd<T> &d = row_shot(shots, rows, nshot, total, stress_sweeps_up<MODE>(), p);
+    const ShotFwd<T> &d = row_shot(shots, rows, nshot, total, block, stress_sweeps_up<MODE>(), p);
     const Grid<T> G = d.G;
     const Inject<T> src = d.src;
     const TileIO<T> io = d.io;
