@@ -16,7 +16,7 @@
 //   grid             rows    tile sweep   vel_cell / stress_cell
 //   32^3              6.9       14.5        15.1
 //   64^3             10.3       19.5        19.4
-//   149 x 101 x 87   32.2       40.7        73.9
+//   149 x 101 x 87   31.0       40.7        73.9
 //   128^3            35.9       45.7        69.8   (7.0 TB/s of 120 B per cell)
 //   192 x 192 x 128  88.7       94.3
 //   256^3           448        364
