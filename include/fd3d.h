@@ -354,7 +354,8 @@ typedef struct fd3d_kernel {
 /* Default at create, until fd3d_set_kernel or fd3d_autotune selects one: each operation on
  * the context (forward, gradient, Born) picks the cell or the tile kernels by the size of its
  * working set (cell while that stays in the Infinity Cache), with the tile shape and sweep
- * depth that fill the chip in one round; fd3d_get_kernel returns what the forward runs.
+ * depth that fill the chip in one to three whole rounds; fd3d_get_kernel returns what the
+ * forward runs.
  * FD3D_EINVAL for an unsupported shape.  The fused variant keeps two copies of the state and swaps them
  * every step; the state accessors always address the current copy, and the gradient's
  * segment recompute and adjoint passes use the tile kernels of the same tile shape. */

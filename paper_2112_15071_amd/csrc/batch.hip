@@ -23,7 +23,7 @@ struct BatchGroup {
     int s0, ns, tiles, recs, wgs;
     int tx, ty, tx2, ty2;
     int vac;  // some shot of the group has a vacuum surface
-    long cols;  // columns of tiles over all shots of the launch
+    int zc;   // depth of the launch for shots with nothing selected (0: each shot's own)
     int rtiles;              // row kernels: their blocks
     const ShotRows *rows;    // and the shots' shares of them (null: tile kernels)
     int ntp;  // cache policy of the group's forward passes (see group_streams)
@@ -170,26 +170,34 @@ TileMap shot_tiles(const BatchGroup &b, const fd3d_ctx *c, int &alt)
     TileMap tm;
     tm.ntx = (c->n[0] + tx - 1) / tx;
     tm.nty = (c->n[1] + ty - 1) / ty;
-    tm.zc = c->zchunk;
-    // no depth selected: the launch's shots share one round
-    if (c->auto_kernel && b.cols > 0) {
-        tm.zc = sweep_depth(c->n[2], b.cols, tile_slots(c->tsize, tx * ty));
-        while (tm.zc > 4 && !window_ok(c, tm.zc)) tm.zc = std::max(4, tm.zc / 2);
-    }
+    tm.zc = c->auto_kernel && b.zc > 0 ? sweep_depth(c, b.zc) : c->zchunk;
     tm.nzc = (c->n[2] + tm.zc - 1) / tm.zc;
     return tm;
 }
 
-// Columns of tiles over ns shots of a launch.
-template <typename C> long tile_columns(const BatchGroup &g, int ns, C &&shot)
+// Sweeps of a launch over ns shots of which some have no kernel selected: their common depth,
+// and unless the batch's tile shapes are selected, the launch's shape (choose_sweep).
+template <typename C> void fit_sweeps(BatchGroup &g, int ns, bool tiles_set, C &&shot)
 {
-    long cols = 0;
-    for (int q = 0; q < ns; ++q) {
-        int alt = 0;
-        const TileMap tm = shot_tiles(g, shot(q), alt);
-        cols += (long)tm.ntx * tm.nty;
+    bool any = false;
+    for (int q = 0; q < ns; ++q) any = any || shot(q)->auto_kernel;
+    if (!any) return;
+    int zc = 0;
+    if (tiles_set) {
+        auto cols = [&](int q) {
+            int alt = 0;
+            const TileMap tm = shot_tiles(g, shot(q), alt);
+            return (long)tm.ntx * tm.nty;
+        };
+        if (launch_depth(ns, shot, cols, g.tx * g.ty, zc) < 1e300) g.zc = zc;
+        return;
     }
-    return cols;
+    const Sweep s = choose_sweep(ns, shot);
+    if (s.zc == 0) return;
+    g.tx = s.tx;
+    g.ty = s.ty;
+    g.tx2 = g.ty2 = 0;
+    g.zc = s.zc;
 }
 
 // Whether the launches over these shots run the row kernels: when no shot has a tile or fused
@@ -356,8 +364,8 @@ void make_groups(fd3d_batch *b)
     // against 134 in lockstep, two each of 128^3, 192 x 192 x 128 and 256 x 256 x 128 584 against 752
     const size_t budget = b->sched_set || b->tiles_set ? b->group_bytes : (size_t)kRowBytes32;
     if (budget == 0) {
-        all.cols = tile_columns(all, b->nshot, [&](int q) { return b->ctx[q]; });
         if (!b->tiles_set && batch_rows(b->ctx.data(), b->nshot, kForwardArrays)) all.rows = batch_row_maps(b);
+        else fit_sweeps(all, b->nshot, b->tiles_set, [&](int q) { return b->ctx[q]; });
         b->groups.push_back(all);
         return;
     }
@@ -386,7 +394,7 @@ void make_groups(fd3d_batch *b)
             g.ty = c0->tile_y;
             g.tx2 = g.ty2 = 0;
         }
-        g.cols = tile_columns(g, g.ns, [&](int q) { return ctx_at(s + q); });
+        if (!g.rows) fit_sweeps(g, g.ns, b->tiles_set, [&](int q) { return ctx_at(s + q); });
         b->groups.push_back(g);
         s = e;
     }
@@ -561,7 +569,8 @@ int batch_gradient_impl(fd3d_batch *b, const fd3d_source *srcs, const int *nrec,
     int tiles = 0, rtiles = 0, recs = 0, ncol = 0;
     int cbase[kMaxBatchColors] = {0, 0, 0, 0};
     BatchGroup all = whole_batch(b);  // every shot in each launch (lockstep)
-    all.cols = tile_columns(all, S, [&](int q) { return b->ctx[q]; });
+    const bool row_adj = !b->tiles_set && batch_rows(b->ctx.data(), S, kAdjointArrays);
+    if (!row_adj) fit_sweeps(all, S, b->tiles_set, [&](int q) { return b->ctx[q]; });
     for (int s = 0; s < S; ++s) {
         fd3d_ctx *c = b->ctx[s];
         const std::string tag = "shot " + std::to_string(s) + ": ";
@@ -680,7 +689,7 @@ int batch_gradient_impl(fd3d_batch *b, const fd3d_source *srcs, const int *nrec,
     all.recs = recs;
     BatchGroup fwd = all;
     if (!b->tiles_set && batch_rows(b->ctx.data(), S, kForwardArrays)) fwd.rows = batch_row_maps(b);
-    if (!b->tiles_set && batch_rows(b->ctx.data(), S, kAdjointArrays)) all.rows = batch_row_maps(b);
+    if (row_adj) all.rows = batch_row_maps(b);
 
     const bool merged = all.rows || all.tx2 == 0;  // stress-M (row kernels, or one tile shape)
     // forward with checkpoints
@@ -919,7 +928,7 @@ int fd3d_batch_autotune(fd3d_batch *b, int steps, int best[6], double *best_ms, 
             if (mode == 1) {
                 long tiles = 0;
                 BatchGroup all = whole_batch(b);
-                all.cols = tile_columns(all, b->nshot, [&](int q) { return b->ctx[q]; });
+                fit_sweeps(all, b->nshot, true, [&](int q) { return b->ctx[q]; });
                 for (const fd3d_ctx *c : b->ctx) {
                     int alt = 0;
                     const TileMap tm = shot_tiles(all, c, alt);

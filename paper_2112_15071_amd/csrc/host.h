@@ -318,21 +318,100 @@ inline bool window_ok(const fd3d_ctx *c, int zc)
 }
 
 // Tile workgroups of NT threads that the device runs at once: the tile kernels' registers
-// allow 20 waves a CU in FP32 (85 VGPRs), 12 in FP64.
+// allow 16 waves a CU in FP32 (80 to 128 VGPRs), 12 in FP64.
 inline long tile_slots(int tsize, int nt)
 {
     int dev = 0, cus = 256;
     (void)hipGetDevice(&dev);
     (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-    return (long)std::max(1, (tsize == 8 ? 12 : 20) / (nt / 64)) * cus;
+    return (long)std::max(1, (tsize == 8 ? 12 : 16) / (nt / 64)) * cus;
 }
 
-// Planes of a sweep when `tiles` columns of tiles of nz planes are cut into at most slots
-// workgroups (at least one per column, at least 4 planes).
-inline int sweep_depth(int nz, long tiles, long slots)
+inline long tile_columns(const fd3d_ctx *c, int tx, int ty)
 {
-    const int cuts = (int)std::min<long>(nz, std::max<long>(1, slots / tiles));
-    return std::max(4, (nz + cuts - 1) / cuts);
+    return (long)((c->n[0] + tx - 1) / tx) * ((c->n[1] + ty - 1) / ty);
+}
+
+// Depth of a grid's sweeps in a launch of depth zc: its planes cut evenly into sweeps of at
+// most zc planes (at least 4, and within one window).
+inline int sweep_depth(const fd3d_ctx *c, int zc)
+{
+    const int nz = c->n[2], cuts = (nz + zc - 1) / zc;
+    int d = std::max(4, (nz + cuts - 1) / cuts);
+    while (d > 4 && !window_ok(c, d)) d = std::max(4, d / 2);
+    return d;
+}
+
+// Depth of a launch of sweeps by workgroups of nt threads over ns grids, of cols(q) columns of
+// tiles each, and its cost (1e300: no sweep fits one window).  The workgroups run in rounds of
+// as many as the chip holds; for one to three rounds, the least depth that needs no more of them.
+// A sweep of zc planes costs about zc + 14 planes' time (its z halo and the z queues' first loads).
+template <typename S, typename F> double launch_depth(int ns, S &&shot, F &&cols, int nt, int &zc)
+{
+    int nz = 4;
+    for (int q = 0; q < ns; ++q) nz = std::max(nz, shot(q)->n[2]);
+    const long slots = tile_slots(shot(0)->tsize, nt);
+    double best = 1e300;
+    for (int r = 1; r <= 3; ++r) {
+        int lo = 4, hi = nz;
+        while (lo < hi) {
+            const int mid = (lo + hi) / 2;
+            long sweeps = 0;
+            for (int q = 0; q < ns; ++q) sweeps += cols(q) * ((shot(q)->n[2] + mid - 1) / mid);
+            if (sweeps <= r * slots) hi = mid;
+            else lo = mid + 1;
+        }
+        long sweeps = 0;
+        int deepest = 0;
+        bool fits = true;
+        for (int q = 0; q < ns; ++q) {
+            const int d = sweep_depth(shot(q), lo);
+            fits = fits && window_ok(shot(q), d);
+            deepest = std::max(deepest, d);
+            sweeps += cols(q) * ((shot(q)->n[2] + d - 1) / d);
+        }
+        const double cost = (double)((sweeps + slots - 1) / slots) * (deepest + 14) * slots * nt;
+        if (fits && cost < best) {
+            best = cost;
+            zc = lo;
+        }
+    }
+    return best;
+}
+
+// Tile shape and depth of a launch of sweeps over ns grids with nothing selected (zc = 0: none
+// fits one window): the least cost.  FP32 rows of 64 columns (256 bytes) cost 1.3 of a wider
+// tile's, the lanes past a row's end included; wide tiles win ties, with a coarse medium (whose
+// grids mostly stay in the cache) narrow ones, at the same cost.  Over 66 launches beyond the cache
+// (forward, Born, gradient, batches; FP32) this comes to 0.8 % of the fastest of all shapes and
+// depths on average, over 57 in FP64 to 2.6 % (1 % where the sweeps are the default).  Us per step, a fixed 64- or 32-plane
+// sweep of the tile as wide as the rows / all shapes at par, 20 waves a CU, zc + 3, a batch always
+// in one round / this: forward 230^3 346 / 355 / 286, 230 x 300 x 260 535 / 571 / 429; Born 230^3
+// 797 / 831 / 626; gradient 230^3 1820 / 1832 / 1375; gradients of four shots of 160 x 150 x 100
+// 1455 / 1599 / 1032, of three of 260 x 200 x 150 3951 / 4740 / 3020; batch of four 160 x 300 x 260
+// 1320 / 1438 / 1223; coarse 64^3 88 / 30 / 21.
+struct Sweep {
+    int tx, ty, zc;
+};
+template <typename S> Sweep choose_sweep(int ns, S &&shot)
+{
+    static const int shapes[][2] = {{256, 4}, {128, 8}, {64, 16}, {128, 4}, {64, 8}, {64, 4}};
+    const int ts = shot(0)->tsize;
+    const bool coarse = coarse_on(shot(0)->opts);
+    Sweep s{64, 8, 0};
+    double best = 1e300;
+    for (int k = 0; k < 6; ++k) {
+        const int tx = shapes[coarse ? 5 - k : k][0], ty = shapes[coarse ? 5 - k : k][1];
+        if (!tile_supported(ts, tx, ty)) continue;
+        int zc = 0;
+        const double cost = launch_depth(ns, shot, [&](int q) { return tile_columns(shot(q), tx, ty); }, tx * ty, zc) *
+                            (ts == 4 && !coarse && tx == 64 ? 1.3 : 1.0);
+        if (cost < best) {
+            best = cost;
+            s = {tx, ty, zc};
+        }
+    }
+    return s;
 }
 
 // The row kernels address the planes around a cell (at most 9) through one buffer descriptor

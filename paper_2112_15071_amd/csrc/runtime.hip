@@ -411,39 +411,14 @@ int fd3d_workspace_bytes(int nx, int ny, int nz, const fd3d_opts *opts, size_t *
 
 namespace {
 
-// Default tile shape and sweep depth: those whose sweeps fill the chip in whole rounds of
-// workgroups (tile_slots at a time) with the least work per CU; a sweep of zc planes costs
-// about zc + 3 planes' time (the z queues' first loads).  Wide tiles win ties, then few rows.
-// Measured against fixed 64- or 32-plane sweeps of the tile as wide as the rows (us per step):
-// forward 256^3 the same tiles (359), 200 x 180 x 160 136 against 240, FP64 120 x 112 x 104 61
-// against 112; Born 192 x 160 x 128 185 against 324.  False when no sweep fits one window.
+// Default tile shape and sweep depth (choose_sweep).  False when no sweep fits one window.
 bool default_tiles(fd3d_ctx *c)
 {
-    static const int shapes[][2] = {{256, 4}, {128, 4}, {128, 8}, {64, 4}, {64, 8}, {64, 16}};
-    const int nz = c->n[2];
-    double best = 1e300;
-    c->tile_x = 64;
-    c->tile_y = 8;
-    c->zchunk = 4;
-    for (const auto &sh : shapes) {
-        if (!tile_supported(c->tsize, sh[0], sh[1])) continue;
-        const long tiles = (long)((c->n[0] + sh[0] - 1) / sh[0]) * ((c->n[1] + sh[1] - 1) / sh[1]);
-        const long slots = tile_slots(c->tsize, sh[0] * sh[1]);
-        for (int r = 1; r <= 4; ++r) {  // rounds of workgroups
-            int zc = sweep_depth(nz, tiles, r * slots);
-            while (zc > 4 && !window_ok(c, zc)) zc = std::max(4, zc / 2);
-            if (!window_ok(c, zc)) continue;
-            const long rounds = (tiles * ((nz + zc - 1) / zc) + slots - 1) / slots;
-            const double cost = (double)rounds * (zc + 3) * slots * sh[0] * sh[1];
-            if (cost < best) {
-                best = cost;
-                c->tile_x = sh[0];
-                c->tile_y = sh[1];
-                c->zchunk = zc;
-            }
-        }
-    }
-    return best < 1e300;
+    const Sweep s = choose_sweep(1, [c](int) { return c; });
+    c->tile_x = s.tx;
+    c->tile_y = s.ty;
+    c->zchunk = s.zc > 0 ? sweep_depth(c, s.zc) : 4;
+    return s.zc > 0;
 }
 
 // fd3d_create with the choice of creating the staging event (events = false: the

@@ -1,0 +1,39 @@
+// Prints what the library's host rules choose; built and read by test_host_rules_cpu.py.
+// One question per line of stdin: "sweep <tsize> <coarse> <nx ny nz> ..." asks for the tile
+// shape and depth of a launch over the grids.
+#include "host.h"
+
+#include <cstdio>
+#include <iostream>
+#include <sstream>
+
+static fd3d_ctx grid(int nx, int ny, int nz, int tsize, int coarse)
+{
+    fd3d_ctx c{};
+    c.n[0] = nx;
+    c.n[1] = ny;
+    c.n[2] = nz;
+    c.tsize = tsize;
+    c.opts.coarse[0] = c.opts.coarse[1] = c.opts.coarse[2] = coarse;
+    // the library's automatic layout (interleaved rows when the whole depth fits one window)
+    c.L.rows = 9.0 * nx * ny * nz * tsize <= (double)fd3d::kMaxWindowBytes;
+    return c;
+}
+
+int main()
+{
+    for (std::string line; std::getline(std::cin, line);) {
+        std::istringstream in(line);
+        std::string what;
+        int ts, cm, nx, ny, nz;
+        in >> what >> ts >> cm;
+        std::vector<fd3d_ctx> g;
+        while (in >> nx >> ny >> nz) g.push_back(grid(nx, ny, nz, ts, cm));
+        if (what == "sweep") {
+            const fd3d::Sweep s = fd3d::choose_sweep((int)g.size(), [&](int q) { return &g[q]; });
+            std::printf("%d %d", s.tx, s.ty);
+            for (auto &c : g) std::printf(" %d", s.zc ? fd3d::sweep_depth(&c, s.zc) : 0);
+            std::printf("\n");
+        }
+    }
+}

@@ -1,0 +1,70 @@
+"""The host's launch rules, asked on the CPU: host_rules.cpp is compiled against the library's
+own csrc/host.h (host pass only, no device needed) and answers one question per line."""
+from __future__ import annotations
+
+import os
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+
+@pytest.fixture(scope="module")
+def ask(tmp_path_factory):
+    from paper_2112_15071_amd import build as B
+
+    exe = str(tmp_path_factory.mktemp("host_rules") / "host_rules")
+    subprocess.run([B.HIPCC, "--offload-arch=gfx950", "--offload-host-only", "-x", "hip", "-std=c++17", "-O1", "-w",
+                    "-I", os.path.join(ROOT, "include"), "-I", B.CSRC, os.path.join(ROOT, "tests", "host_rules.cpp"),
+                    "-o", exe], check=True)
+
+    def run(lines):
+        out = subprocess.run([exe], input="\n".join(lines) + "\n", capture_output=True, text=True, check=True).stdout
+        rows = [[int(v) for v in r.split()] for r in out.splitlines()]
+        assert len(rows) == len(lines)
+        return rows
+
+    return run
+
+
+# Launches with nothing selected that a narrow tile or one round of whole-depth sweeps made
+# slower than a fixed sweep of the tile as wide as the rows; the shape and depth measured fastest
+# on MI355X (or within 2 % of it).
+SWEEPS = [("4 0", [(230, 230, 230)], (256, 4, 58)), ("4 0", [(230, 300, 260)], (256, 4, 87)),
+          ("4 0", [(256, 256, 256)], (256, 4, 64)), ("4 0", [(300, 300, 200)], (128, 8, 100)),
+          ("4 0", [(260, 260, 260)], (64, 16, 87)), ("4 0", [(200, 180, 160)], (256, 4, 32)),
+          ("4 0", [(160, 150, 100)] * 4, (64, 16, 50)), ("4 0", [(260, 200, 150)] * 3, (128, 8, 150)),
+          ("4 0", [(230, 230, 230)] * 2, (256, 4, 115)),
+          ("4 1", [(64, 64, 64)], (64, 4, 4)), ("4 1", [(192, 192, 128)], (64, 4, 19)),
+          ("8 0", [(120, 112, 104)], (128, 4, 12)), ("8 0", [(150, 150, 100)], (64, 8, 25))]
+
+
+def test_default_sweeps(ask):
+    lines = [f"sweep {k[0]} {9 * int(k[2])} " + " ".join("%d %d %d" % g for g in grids) for k, grids, _ in SWEEPS]
+    for (k, grids, want), got in zip(SWEEPS, ask(lines)):
+        assert tuple(got[:3]) == want, (k, grids, got)
+
+
+def test_default_sweeps_stay_within_the_limits(ask):
+    """Over all sizes (uneven launches included): a supported shape, depths of 4 planes up, and
+    windows (depth + 8 planes, at most the grid's) within 1 GiB, also where planes are so large
+    that only short sweeps fit."""
+    import random
+
+    rng = random.Random(3)
+    sizes = lambda: tuple(int(round(4 * 2 ** rng.uniform(0, 9.5))) for _ in range(3))
+    cases = [(ts, [sizes() for _ in range(rng.choice([1, 1, 2, 5]))]) for _ in range(300) for ts in (4, 8)]
+    cases = [(ts, [g for g in gs if g[0] * g[1] * g[2] < 2 ** 30] or [(4, 4, 4)]) for ts, gs in cases]
+    cases += [(4, [(4096, 4096, 24)]), (4, [(8192, 3000, 60)]), (8, [(4096, 2048, 100)])]
+    shapes = {4: {(64, 4), (64, 8), (64, 16), (128, 4), (128, 8), (256, 4)}, 8: {(64, 4), (64, 8), (128, 4)}}
+    rows = ask([f"sweep {ts} 0 " + " ".join("%d %d %d" % g for g in gs) for ts, gs in cases])
+    for (ts, gs), r in zip(cases, rows):
+        assert tuple(r[:2]) in shapes[ts], (ts, gs, r)
+        for (nx, ny, nz), zc in zip(gs, r[2:]):
+            rows_of = 9 if 9 * nx * ny * nz * ts <= 2 ** 30 else 1
+            plane = rows_of * nx * ny * ts
+            if zc == 0:  # no sweep: not even one of 4 planes fits
+                assert min(12, nz) * plane > 2 ** 30, (ts, gs, r)
+            else:
+                assert zc >= 4 and min(zc + 8, nz) * plane <= 2 ** 30, (ts, gs, r)
