@@ -75,11 +75,16 @@ int born_impl(fd3d_ctx *c, fd3d_ctx *dc, const fd3d_source *src, const void *dla
         ios.acc[1] = (T *)dmu;
         const bool ntp = sizeof(T) == 4 && stream_model(c);  // cache policy, as in launch_pass
         const RowMap rm = row_map(c);
-        const dim3 gv = row_grid(rm), gs = row_grid(rm, recg.nq + recd.nq);
+        const dim3 gv = row_grid(rm), gr = row_grid(rm, recg.nq + recd.nq);
+        const bool carried = gr.x > 0;  // else more receivers than the launch has blocks for
+        const dim3 gs = carried ? gr : gv;
+        const RecJob<T> none{};
         for (int n = 0; n < c->nt; ++n) {
             if (kern == Kern::rows) {
                 vel_row_io<T, kBornV><<<gv, 256, 0, st>>>(G, inj, n, rm, iov);
-                stress_row_io<T, kBornS><<<gs, 256, 0, st>>>(G, inj, n, rm, ios, recg, recd);
+                stress_row_io<T, kBornS><<<gs, 256, 0, st>>>(G, inj, n, rm, ios, carried ? recg : none, carried ? recd : none);
+                for (const RecJob<T> &r : {recg, recd})
+                    if (!carried && r.nq > 0) record<T><<<rec_blocks(r, 256), 256, 0, st>>>(r, n);
                 continue;
             }
             with_tile<T>(c->tile_x, c->tile_y, [&](auto tx, auto ty) {

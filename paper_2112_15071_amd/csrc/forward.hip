@@ -48,6 +48,11 @@ void launch_rows(const fd3d_ctx *c, const Grid<T> &G, const Inject<T> &inj, int 
 {
     const RowMap rm = row_map(c);
     const dim3 g = row_grid(rm), gs = row_grid(rm, rec.nq);
+    if (gs.x == 0) {  // more receivers than the launch has blocks for
+        launch_rows<T, FS>(c, G, inj, n, pass, st, RecJob<T>{});
+        record<T><<<rec_blocks(rec, 256), 256, 0, st>>>(rec, n);
+        return;
+    }
     if (G.save[VX] != nullptr && pass == kPassVel) pass = kPassVelSave;
     if constexpr (!FS) {
         if (G.ks > 0 && pass != kPassVelSave) {
@@ -331,6 +336,7 @@ int fd3d_autotune(fd3d_ctx *ctx, int steps, fd3d_kernel *best, double *best_ms, 
         if (sh[1] > 64 && ctx->n[0] < sh[1] / 2) continue;  // mostly idle lanes
         for (int zc : chunks) {
             if (sh[0] == FD3D_KERNEL_CELL && zc != chunks[0]) break;  // no z chunks
+            if (sh[0] == FD3D_KERNEL_CELL && !rows_ok(ctx) && !cells_ok(ctx)) break;
             if (sh[0] == FD3D_KERNEL_FUSED && zc < 8) continue;
             if (zc > ctx->n[2] && zc != chunks[0]) continue;
             if (!window_ok(ctx, zc)) continue;

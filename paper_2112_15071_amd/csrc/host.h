@@ -414,32 +414,6 @@ template <typename S> Sweep choose_sweep(int ns, S &&shot)
     return s;
 }
 
-// The row kernels address the planes around a cell (at most 9) through one buffer descriptor
-// per field; the cell variant of a context whose planes are too large for that runs the
-// kernels with a bounds test per load.
-inline bool rows_ok(const fd3d_ctx *c) { return window_ok(c, 1); }
-
-// Kernels of an operation that steps `arrays` cell-sized arrays: rows, tile sweeps, or the
-// kernels with a bounds test per load (cells).  A selected variant decides; with nothing
-// selected, the rows run while the arrays stay in the Infinity Cache, and else the sweeps.
-// Measured on both sides of the limit (FP32, MI355X, us per step, rows / best tile sweep): the
-// forward's 12 arrays at 192 x 192 x 128 (226 MB) 89 / 94 and 256 x 256 x 96 (302 MB) 156 / 133;
-// Born's 24 at 128^3 (201 MB) 74 / 94 and 192 x 160 x 128 (377 MB) 210 / 185; the adjoint's 29 at
-// 149 x 101 x 87 (152 MB) 159 / 183, 128^3 (243 MB) 201 / 202 and 192 x 160 x 128 (456 MB)
-// 380 / 369 (whole gradients).  FP64 rows hold twice the registers and halve the waves in
-// flight: 48^3 14.7 / 22.4, 120 x 112 x 104 (134 MB) 71 / 61.
-constexpr int kForwardArrays = 12, kBornArrays = 24, kAdjointArrays = 29;
-constexpr double kRowBytes32 = 230.0 * 1024 * 1024, kRowBytes64 = 64.0 * 1024 * 1024;
-enum class Kern { rows, tiles, cells };
-inline Kern kernels_of(const fd3d_ctx *c, int arrays)
-{
-    if (!c->auto_kernel)
-        return c->variant != FD3D_KERNEL_CELL ? Kern::tiles : rows_ok(c) ? Kern::rows : Kern::cells;
-    if (coarse_on(c->opts)) return Kern::tiles;
-    const double bytes = (double)arrays * c->n[0] * c->n[1] * c->n[2] * c->tsize;
-    return bytes <= (c->tsize == 8 ? kRowBytes64 : kRowBytes32) ? Kern::rows : Kern::tiles;
-}
-
 // Work of a row launch over a grid.  Blocks as wide as the rows, of the width that leaves the
 // fewest lanes idle (the widest of equals; 149 x 101 x 87: 32.2 us a step with 64 columns, 35.6
 // with 256).  Grids whose planes are small are cut into 8 slabs of planes, one per XCD: the few
@@ -474,11 +448,50 @@ inline RowMap row_map(const fd3d_ctx *c, bool list = false)
     return rm;
 }
 
-// Grid of a row launch that also samples nq receiver items.
+// Largest grid of blocks along y and z.
+constexpr int kMaxGridYZ = 65535;
+
+// Grid of a row launch that also samples nq receiver items; none (x = 0) when those do not fit
+// beside the planes.
 inline dim3 row_grid(const RowMap &rm, int nq = 0)
 {
-    const int per = 8 * rm.tiles() * 256;
-    return dim3(8, rm.tiles(), rm.planes() + (nq + per - 1) / per);
+    const long per = 8L * rm.tiles() * 256, z = rm.planes() + (nq + per - 1) / per;
+    return z <= kMaxGridYZ ? dim3(8, rm.tiles(), (unsigned)z) : dim3(0, 1, 1);
+}
+
+// The row kernels address the planes around a cell (at most 9) through one buffer descriptor
+// per field, and deal tiles and planes out along y and z of a grid of blocks; the cell variant of
+// a context whose planes are too large for the one or too many for the other (16 x 4096 x 4200:
+// 128 strips of 4200 planes over 8 XCDs) runs the kernels with a bounds test per load.
+inline bool rows_ok(const fd3d_ctx *c)
+{
+    if (!window_ok(c, 1)) return false;
+    const RowMap rm = row_map(c);
+    return rm.tiles() <= kMaxGridYZ && (long)rm.np * rm.cpx <= kMaxGridYZ;
+}
+
+// Those kernels take a plane along z and four rows along y of a grid of blocks.
+inline bool cells_ok(const fd3d_ctx *c) { return c->n[2] <= kMaxGridYZ && (c->n[1] + 3) / 4 <= kMaxGridYZ; }
+
+// Kernels of an operation that steps `arrays` cell-sized arrays: rows, tile sweeps, or the
+// kernels with a bounds test per load (cells).  A selected variant decides; with nothing
+// selected, the rows run while the arrays stay in the Infinity Cache, and else the sweeps.
+// Measured on both sides of the limit (FP32, MI355X, us per step, rows / best tile sweep): the
+// forward's 12 arrays at 192 x 192 x 128 (226 MB) 89 / 94 and 256 x 256 x 96 (302 MB) 156 / 133;
+// Born's 24 at 128^3 (201 MB) 74 / 94 and 192 x 160 x 128 (377 MB) 210 / 185; the adjoint's 29 at
+// 149 x 101 x 87 (152 MB) 159 / 183, 128^3 (243 MB) 201 / 202 and 192 x 160 x 128 (456 MB)
+// 380 / 369 (whole gradients).  FP64 rows hold twice the registers and halve the waves in
+// flight: 48^3 14.7 / 22.4, 120 x 112 x 104 (134 MB) 71 / 61.
+constexpr int kForwardArrays = 12, kBornArrays = 24, kAdjointArrays = 29;
+constexpr double kRowBytes32 = 230.0 * 1024 * 1024, kRowBytes64 = 64.0 * 1024 * 1024;
+enum class Kern { rows, tiles, cells };
+inline Kern kernels_of(const fd3d_ctx *c, int arrays)
+{
+    if (!c->auto_kernel)
+        return c->variant != FD3D_KERNEL_CELL ? Kern::tiles : rows_ok(c) ? Kern::rows : Kern::cells;
+    if (coarse_on(c->opts)) return Kern::tiles;
+    const double bytes = (double)arrays * c->n[0] * c->n[1] * c->n[2] * c->tsize;
+    return bytes <= (c->tsize == 8 ? kRowBytes64 : kRowBytes32) && rows_ok(c) ? Kern::rows : Kern::tiles;
 }
 
 // Cache policy of a context's single-grid tile launches: the model arrays and the

@@ -1,6 +1,7 @@
 // Prints what the library's host rules choose; built and read by test_host_rules_cpu.py.
 // One question per line of stdin: "sweep <tsize> <coarse> <nx ny nz> ..." asks for the tile
-// shape and depth of a launch over the grids.
+// shape and depth of a launch over the grids, "rows <tsize> <coarse> <nx ny nz> [<receiver items> 1 1]" whether
+// the row kernels take a grid, the map of their launch and its grid of blocks.
 #include "host.h"
 
 #include <cstdio>
@@ -34,6 +35,11 @@ int main()
             std::printf("%d %d", s.tx, s.ty);
             for (auto &c : g) std::printf(" %d", s.zc ? fd3d::sweep_depth(&c, s.zc) : 0);
             std::printf("\n");
+        } else if (what == "rows") {
+            const fd3d::RowMap r = fd3d::row_map(&g[0]);
+            const dim3 b = fd3d::row_grid(r, g.size() > 1 ? g[1].n[0] : 0);
+            std::printf("%d %d %d %d %d %d %d %d %d %u %u %u\n", (int)fd3d::rows_ok(&g[0]), r.lbx, r.ntx, r.rps, r.ns, r.nslab,
+                        r.np, r.cpx, r.tiles(), b.x, b.y, b.z);
         }
     }
 }

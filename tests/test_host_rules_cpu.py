@@ -68,3 +68,33 @@ def test_default_sweeps_stay_within_the_limits(ask):
                 assert min(12, nz) * plane > 2 ** 30, (ts, gs, r)
             else:
                 assert zc >= 4 and min(zc + 8, nz) * plane <= 2 ** 30, (ts, gs, r)
+
+
+def test_row_launches_fit_the_grid_of_blocks(ask):
+    """A row launch covers every row and plane and stays within 65535 blocks along y and z, or the
+    row kernels refuse the grid: tall grids of many strips (16 x 4096 x 4200: 16 pieces of 4200
+    planes per XCD), long thin ones, and random ones.  Receivers that do not fit beside the planes
+    are left to a launch of their own (x = 0)."""
+    import random
+
+    rng = random.Random(5)
+    grids = [(16, 4096, 4200), (16, 4096, 4095), (4, 4, 600000), (4, 100000, 1000), (2000000, 4, 4), (64, 64, 64),
+             (149, 101, 87), (7, 6, 5), (300, 130, 12)]
+    for _ in range(400):
+        g = tuple(int(round(4 * 2 ** rng.uniform(0, 17))) for _ in range(3))
+        if g[0] * g[1] * g[2] < 2 ** 31 - 1:
+            grids.append(g)
+    rows = ask([f"rows 4 0 {x} {y} {z}" for x, y, z in grids])
+    seen = {True: 0, False: 0}
+    for (nx, ny, nz), (ok, lbx, ntx, rps, ns, nslab, np_, cpx, tiles, bx, by, bz) in zip(grids, rows):
+        assert ntx << lbx >= nx and ns * rps * (256 >> lbx) >= ny and nslab * np_ >= nz and 8 * cpx >= ns * nslab
+        assert tiles == rps * ntx
+        if ok:
+            assert (bx, by, bz) == (8, tiles, np_ * cpx) and by <= 65535 and bz <= 65535, (nx, ny, nz)
+        seen[bool(ok)] += 1
+    assert not rows[0][0] and rows[1][0] and not rows[2][0]
+    assert seen[True] > 100 and seen[False] > 10
+    # 64^3 (8 planes per XCD, 16 tiles): 32768 items per layer of blocks
+    per = 8 * 16 * 256
+    few, most, many = ask([f"rows 4 0 64 64 64 {q} 1 1" for q in (1, per * (65535 - 8), per * (65535 - 8) + 1)])
+    assert few[9:] == [8, 16, 9] and most[9:] == [8, 16, 65535] and many[9] == 0
