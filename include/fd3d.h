@@ -304,7 +304,9 @@ int fd3d_batch_set_tiles(fd3d_batch *b, int tile_x, int tile_y, int tile2_x, int
  * last-level cache (256 MB Infinity Cache on MI355X) keeps its fields resident between
  * steps.  A group whose shots all use the tile kernel with one shape of their own
  * (fd3d_set_kernel / fd3d_autotune on each context) launches with that shape; other
- * groups use the batch's shapes.  Results per shot are the same in both orders. */
+ * groups use the batch's shapes when those are selected (fd3d_batch_set_tiles), and else
+ * the cell kernels while the group stays in the cache, or a shape that fits its shots.
+ * Results per shot are the same in both orders. */
 int fd3d_batch_set_schedule(fd3d_batch *b, size_t group_bytes);
 
 /* Times `steps` batched steps past the first (sources and receivers off, one warm-up run
@@ -313,7 +315,8 @@ int fd3d_batch_set_schedule(fd3d_batch *b, size_t group_bytes);
  * 230) and the cache-blocked schedule with group budgets of 96, 128, 192, 256 and 384 MiB;
  * keeps the fastest for later batch calls and writes it to best = {tile_x, tile_y, tile2_x,
  * tile2_y, workgroups (0 = persistent), group MiB (0 = lockstep)} and its ms per step to
- * *best_ms (each when non-NULL).  Every shot's forward state is zeroed afterwards.
+ * *best_ms (each when non-NULL).  With groups the tile shapes are only those of lockstep
+ * launches: they are not selected, so that groups may run the cell kernels.  Every shot's forward state is zeroed afterwards.
  * Synchronises the stream. */
 int fd3d_batch_autotune(fd3d_batch *b, int steps, int best[6], double *best_ms, void *hip_stream);
 

@@ -1,59 +1,11 @@
 // Batches: many contexts (uneven grids, own models, sources and receivers) stepped
 // together, one persistent launch per pass for all shots, optionally captured once as a
 // hipGraph holding the whole nt-step sequence; the batch tuner and the batched gradient.
-//
-// Schedules.  Lockstep: every launch covers every shot, and the shots advance one step
-// at a time together.  Cache-blocked groups: the shots, taken from the smallest working
-// set (nine fields and three model arrays) to the largest, are cut into runs whose
-// working sets add up to at most a given number of bytes; one group runs all its nt
-// steps (one launch per pass over the group's shots) before the next group starts.
-// Sized to the last-level (Infinity) cache, a group's fields stay resident from one step
-// to the next.  Shots are independent, so both schedules give every shot the same result
-// bit for bit.
-#include "host.h"
+#include "batch_plan.h"
 
 #include <new>
 
 using namespace fd3d;
-
-// Shots at positions [s0, s0 + ns) of the batch's schedule order, stepped by one launch
-// per pass: their work items and receiver components (counted from the group's first),
-// the persistent grid size and the tile shapes of the launch (tx2 = 0: one shape).
-struct BatchGroup {
-    int s0, ns, tiles, recs, wgs;
-    int tx, ty, tx2, ty2;
-    int vac;  // some shot of the group has a vacuum surface
-    int zc;   // depth of the launch for shots with nothing selected (0: each shot's own)
-    int rtiles;              // row kernels: their blocks
-    const ShotRows *rows;    // and the shots' shares of them (null: tile kernels)
-    int ntp;  // cache policy of the group's forward passes (see group_streams)
-};
-
-struct fd3d_batch {
-    int nshot;
-    std::vector<fd3d_ctx *> ctx;
-    int tsize, nt, fs;
-    char *ws;
-    size_t ws_bytes;
-    size_t off_fwd, off_rec, off_rows;
-    int tile_x, tile_y, wgs_req;
-    int tile2_x, tile2_y;  // optional second tile shape (same workgroup size), 0: none
-    bool tiles_set;        // the caller or the tuner selected the batch's tile shapes
-    size_t group_bytes;    // 0: lockstep; otherwise the cache-blocked group budget
-    bool sched_set;        // the caller or the tuner selected the schedule
-    std::vector<BatchGroup> groups;
-    std::vector<int> order;  // shot at each position of the descriptor arrays
-    std::vector<unsigned char> fwd_host, rec_host;
-    std::vector<ShotRows> rows_host;
-    hipEvent_t staged;
-    bool staged_pending;
-    hipStream_t cap;
-    std::vector<unsigned char> grad_host;  // batched-gradient descriptors, kept for the async upload
-    hipGraph_t graph;
-    hipGraphExec_t gexec;
-    bool graph_valid;
-    long graph_key;
-};
 
 namespace {
 
@@ -96,13 +48,6 @@ template <typename T, typename F> decltype(auto) with_batch_tiles(const BatchGro
     return f(X128{}, Y4{}, X64{}, Y8{});
 }
 
-// Two contexts whose batched passes read the same model arrays: the caller's, in place,
-// or one copy in interleaved rows (see share_model).
-bool shares_model(const fd3d_ctx *a, const fd3d_ctx *b)
-{
-    return a->L.rows == b->L.rows && (a->lam == b->lam || a->mu == b->mu || a->rho == b->rho);
-}
-
 // A context with interleaved rows reads its own copy of the model.  In a batch, the shots
 // whose contexts were created over the same caller arrays with the same grid and type hold
 // identical copies in the same layout, and all read the copy of the first such shot: one
@@ -122,104 +67,6 @@ template <typename T> void share_model(Grid<T> &G, const fd3d_ctx *c, fd3d_ctx *
         }
     }
 }
-
-// Streaming (non-temporal) policy for the forward passes of a group of contexts, as
-// stream_model for one grid: FP32, the group's working sets add up to more than the
-// Infinity Cache, and no two of its shots share a model array (a shared model is re-read
-// by the other shots' tiles of the same launch).
-bool group_streams(const fd3d_ctx *const *ctx, int ns)
-{
-    if (ns < 1 || ctx[0]->tsize != 4) return false;
-    double bytes = 0.0;
-    for (int q = 0; q < ns; ++q) {
-        bytes += 12.0 * (double)ctx[q]->n[0] * (double)ctx[q]->n[1] * (double)ctx[q]->n[2] * (double)ctx[q]->tsize;
-        for (int r = 0; r < q; ++r)
-            if (shares_model(ctx[q], ctx[r])) return false;
-    }
-    return bytes > kInfinityCacheBytes;
-}
-
-// The batch's own tile shapes as one group covering every shot (counts not filled in).
-BatchGroup whole_batch(const fd3d_batch *b)
-{
-    BatchGroup g{};
-    g.s0 = 0;
-    g.ns = b->nshot;
-    g.tx = b->tile_x;
-    g.ty = b->tile_y;
-    g.tx2 = b->tile2_x;
-    g.ty2 = b->tile2_y;
-    g.ntp = group_streams(b->ctx.data(), b->nshot);
-    return g;
-}
-
-// Tile map of one shot of a launch, and whether it uses the launch's second tile shape
-// (when that covers its rows with fewer idle columns).
-TileMap shot_tiles(const BatchGroup &b, const fd3d_ctx *c, int &alt)
-{
-    int tx = b.tx, ty = b.ty;
-    alt = 0;
-    if (b.tx2 > 0) {
-        const int pad1 = (c->n[0] + tx - 1) / tx * tx, pad2 = (c->n[0] + b.tx2 - 1) / b.tx2 * b.tx2;
-        if (pad2 < pad1) {
-            alt = 1;
-            tx = b.tx2;
-            ty = b.ty2;
-        }
-    }
-    TileMap tm;
-    tm.ntx = (c->n[0] + tx - 1) / tx;
-    tm.nty = (c->n[1] + ty - 1) / ty;
-    tm.zc = c->auto_kernel && b.zc > 0 ? sweep_depth(c, b.zc) : c->zchunk;
-    tm.nzc = (c->n[2] + tm.zc - 1) / tm.zc;
-    return tm;
-}
-
-// Sweeps of a launch over ns shots of which some have no kernel selected: their common depth,
-// and unless the batch's tile shapes are selected, the launch's shape (choose_sweep).
-template <typename C> void fit_sweeps(BatchGroup &g, int ns, bool tiles_set, C &&shot)
-{
-    bool any = false;
-    for (int q = 0; q < ns; ++q) any = any || shot(q)->auto_kernel;
-    if (!any) return;
-    int zc = 0;
-    if (tiles_set) {
-        auto cols = [&](int q) {
-            int alt = 0;
-            const TileMap tm = shot_tiles(g, shot(q), alt);
-            return (long)tm.ntx * tm.nty;
-        };
-        if (launch_depth(ns, shot, cols, g.tx * g.ty, zc) < 1e300) g.zc = zc;
-        return;
-    }
-    const Sweep s = choose_sweep(ns, shot);
-    if (s.zc == 0) return;
-    g.tx = s.tx;
-    g.ty = s.ty;
-    g.tx2 = g.ty2 = 0;
-    g.zc = s.zc;
-}
-
-// Whether the launches over these shots run the row kernels: when no shot has a tile or fused
-// kernel selected and the arrays of all of them (`arrays` per shot) together stay in the
-// Infinity Cache (kernels_of).  In lockstep, us per step, rows / best tile sweep (with the depth
-// of one round), forward and gradient: six shots of 40 x 50 x 60 30.0 / 31.6 and 112.9 / 133.6,
-// eight of 64^3 46.7 / 50.6 and 208.7 / 212.1, four of 96 x 80 x 72 (106 MB) 54.1 / 54.3 and 244.2
-// / 244.3, four of 128 x 96 x 80 (189 MB) 71.5 / 79.7 and 342.3 / 348.2.
-bool batch_rows(const fd3d_ctx *const *ctx, int ns, int arrays)
-{
-    double bytes = 0.0;
-    if (ns == 1 && arrays == kForwardArrays) return kernels_of(ctx[0], arrays) == Kern::rows;
-    for (int q = 0; q < ns; ++q) {
-        const fd3d_ctx *c = ctx[q];
-        if (!rows_ok(c) || (!c->auto_kernel && c->variant != FD3D_KERNEL_CELL)) return false;
-        bytes += (double)arrays * c->n[0] * c->n[1] * c->n[2] * c->tsize;
-    }
-    return bytes <= (ctx[0]->tsize == 8 ? kRowBytes64 : kRowBytes32);
-}
-
-// Where the batch workspace holds the shots' row maps.
-const ShotRows *batch_row_maps(const fd3d_batch *b) { return (const ShotRows *)(b->ws + b->off_rows); }
 
 // One pass over a group with the row kernels.
 template <typename T, bool FS>
@@ -345,59 +192,6 @@ template <typename T> int batch_sequence(fd3d_batch *b, int flags, hipStream_t s
     }
     HIP_TRY(hipGetLastError());
     return FD3D_OK;
-}
-
-// Working set of one shot in the step loop: nine fields and the three model arrays.
-size_t shot_footprint(const fd3d_ctx *c) { return (size_t)12 * c->n[0] * c->n[1] * c->n[2] * c->tsize; }
-
-// Groups of the batch's schedule and their tile shapes.  A cache-blocked group whose
-// shots all run the tile kernel with one shape of their own uses that shape (each
-// shot's tuned kernel); otherwise a group uses the batch's shapes.
-void make_groups(fd3d_batch *b)
-{
-    b->groups.clear();
-    b->order.resize(b->nshot);
-    for (int s = 0; s < b->nshot; ++s) b->order[s] = s;
-    BatchGroup all = whole_batch(b);
-    // with neither schedule nor tile shapes selected, groups that stay in the Infinity Cache
-    // (one shot per group where a shot alone exceeds it): three shots of 128^3 118.4 us per step
-    // against 134 in lockstep, two each of 128^3, 192 x 192 x 128 and 256 x 256 x 128 584 against 752
-    const size_t budget = b->sched_set || b->tiles_set ? b->group_bytes : (size_t)kRowBytes32;
-    if (budget == 0) {
-        if (!b->tiles_set && batch_rows(b->ctx.data(), b->nshot, kForwardArrays)) all.rows = batch_row_maps(b);
-        else fit_sweeps(all, b->nshot, b->tiles_set, [&](int q) { return b->ctx[q]; });
-        b->groups.push_back(all);
-        return;
-    }
-    std::stable_sort(b->order.begin(), b->order.end(),
-                     [&](int x, int y) { return shot_footprint(b->ctx[x]) < shot_footprint(b->ctx[y]); });
-    auto ctx_at = [&](int p) { return b->ctx[b->order[p]]; };
-    int s = 0;
-    while (s < b->nshot) {
-        BatchGroup g = all;
-        g.s0 = s;
-        size_t bytes = shot_footprint(ctx_at(s));
-        int e = s + 1;
-        while (e < b->nshot && bytes + shot_footprint(ctx_at(e)) <= budget) bytes += shot_footprint(ctx_at(e++));
-        g.ns = e - s;
-        std::vector<const fd3d_ctx *> members;
-        for (int q = s; q < e; ++q) members.push_back(ctx_at(q));
-        g.ntp = group_streams(members.data(), g.ns);
-        if (batch_rows(members.data(), g.ns, kForwardArrays)) g.rows = batch_row_maps(b) + g.s0;
-        const fd3d_ctx *c0 = ctx_at(s);
-        auto tiled = [](const fd3d_ctx *c) { return c->variant == FD3D_KERNEL_TILE || c->auto_kernel; };
-        bool same = tiled(c0);
-        for (int q = s + 1; q < e && same; ++q)
-            same = tiled(ctx_at(q)) && ctx_at(q)->tile_x == c0->tile_x && ctx_at(q)->tile_y == c0->tile_y;
-        if (same && tile_supported(b->tsize, c0->tile_x, c0->tile_y)) {
-            g.tx = c0->tile_x;
-            g.ty = c0->tile_y;
-            g.tx2 = g.ty2 = 0;
-        }
-        if (!g.rows) fit_sweeps(g, g.ns, b->tiles_set, [&](int q) { return ctx_at(s + q); });
-        b->groups.push_back(g);
-        s = e;
-    }
 }
 
 template <typename T>
@@ -569,7 +363,7 @@ int batch_gradient_impl(fd3d_batch *b, const fd3d_source *srcs, const int *nrec,
     int tiles = 0, rtiles = 0, recs = 0, ncol = 0;
     int cbase[kMaxBatchColors] = {0, 0, 0, 0};
     BatchGroup all = whole_batch(b);  // every shot in each launch (lockstep)
-    const bool row_adj = !b->tiles_set && batch_rows(b->ctx.data(), S, kAdjointArrays);
+    const bool row_adj = batch_rows(b->tiles_set, b->ctx.data(), S, kAdjointArrays);
     if (!row_adj) fit_sweeps(all, S, b->tiles_set, [&](int q) { return b->ctx[q]; });
     for (int s = 0; s < S; ++s) {
         fd3d_ctx *c = b->ctx[s];
@@ -688,7 +482,7 @@ int batch_gradient_impl(fd3d_batch *b, const fd3d_source *srcs, const int *nrec,
     all.rtiles = rtiles;
     all.recs = recs;
     BatchGroup fwd = all;
-    if (!b->tiles_set && batch_rows(b->ctx.data(), S, kForwardArrays)) fwd.rows = batch_row_maps(b);
+    if (batch_rows(b->tiles_set, b->ctx.data(), S, kForwardArrays)) fwd.rows = batch_row_maps(b);
     if (row_adj) all.rows = batch_row_maps(b);
 
     const bool merged = all.rows || all.tx2 == 0;  // stress-M (row kernels, or one tile shape)
@@ -951,8 +745,8 @@ int fd3d_batch_autotune(fd3d_batch *b, int steps, int best[6], double *best_ms, 
         }
         if (rc) break;
     }
-    // the schedule, with the winning shapes for the launches that use the batch's shapes: the
-    // batch's own choice (row kernels, groups that stay in the cache), then the budgets
+    // the schedule, with nothing selected but the winning shapes kept for the launches that use the
+    // batch's: the library's own choice (row kernels, groups that stay in the cache), then the budgets
     if (!rc) {
         b->tile_x = win[0];
         b->tile_y = win[1];
@@ -967,7 +761,7 @@ int fd3d_batch_autotune(fd3d_batch *b, int steps, int best[6], double *best_ms, 
             win_set = false;
             win_mib = (int)(kRowBytes32 / (1 << 20));
         }
-        b->tiles_set = b->sched_set = true;
+        b->sched_set = true;
         for (int mib : budgets) {
             if (rc) break;
             b->group_bytes = (size_t)mib << 20;
@@ -977,7 +771,7 @@ int fd3d_batch_autotune(fd3d_batch *b, int steps, int best[6], double *best_ms, 
             if (ms < win_ms) {
                 win_ms = ms;
                 win_mib = mib;
-                win_set = true;
+                win_set = false;
             }
         }
     }

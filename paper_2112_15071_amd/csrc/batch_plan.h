@@ -1,0 +1,220 @@
+// Batches on the host: the batch, and which kernels its launches run in which order.
+//
+// Schedules.  Lockstep: every launch covers every shot, and the shots advance one step
+// at a time together.  Cache-blocked groups: the shots, taken from the smallest working
+// set (nine fields and three model arrays) to the largest, are cut into runs whose
+// working sets add up to at most a given number of bytes; one group runs all its nt
+// steps (one launch per pass over the group's shots) before the next group starts.
+// Sized to the last-level (Infinity) cache, a group's fields stay resident from one step
+// to the next.  Shots are independent, so both schedules give every shot the same result
+// bit for bit.
+#pragma once
+
+#include "host.h"
+
+namespace fd3d {
+
+// Shots at positions [s0, s0 + ns) of the batch's schedule order, stepped by one launch
+// per pass: their work items and receiver components (counted from the group's first),
+// the persistent grid size and the tile shapes of the launch (tx2 = 0: one shape).
+struct BatchGroup {
+    int s0, ns, tiles, recs, wgs;
+    int tx, ty, tx2, ty2;
+    int vac;  // some shot of the group has a vacuum surface
+    int zc;   // depth of the launch for shots with nothing selected (0: each shot's own)
+    int rtiles;              // row kernels: their blocks
+    const ShotRows *rows;    // and the shots' shares of them (null: tile kernels)
+    int ntp;  // cache policy of the group's forward passes (see group_streams)
+};
+
+} // namespace fd3d
+
+struct fd3d_batch {
+    int nshot;
+    std::vector<fd3d_ctx *> ctx;
+    int tsize, nt, fs;
+    char *ws;
+    size_t ws_bytes;
+    size_t off_fwd, off_rec, off_rows;
+    int tile_x, tile_y, wgs_req;
+    int tile2_x, tile2_y;  // optional second tile shape (same workgroup size), 0: none
+    bool tiles_set;        // the caller or the tuner selected the batch's tile shapes
+    size_t group_bytes;    // 0: lockstep; otherwise the cache-blocked group budget
+    bool sched_set;        // the caller or the tuner selected the schedule
+    std::vector<fd3d::BatchGroup> groups;
+    std::vector<int> order;  // shot at each position of the descriptor arrays
+    std::vector<unsigned char> fwd_host, rec_host;
+    std::vector<fd3d::ShotRows> rows_host;
+    hipEvent_t staged;
+    bool staged_pending;
+    hipStream_t cap;
+    std::vector<unsigned char> grad_host;  // batched-gradient descriptors, kept for the async upload
+    hipGraph_t graph;
+    hipGraphExec_t gexec;
+    bool graph_valid;
+    long graph_key;
+};
+
+namespace fd3d {
+
+// Two contexts whose batched passes read the same model arrays: the caller's, in place,
+// or one copy in interleaved rows (see share_model).
+inline bool shares_model(const fd3d_ctx *a, const fd3d_ctx *b)
+{
+    return a->L.rows == b->L.rows && (a->lam == b->lam || a->mu == b->mu || a->rho == b->rho);
+}
+
+// Streaming (non-temporal) policy for the forward passes of a group of contexts, as
+// stream_model for one grid: FP32, the group's working sets add up to more than the
+// Infinity Cache, and no two of its shots share a model array (a shared model is re-read
+// by the other shots' tiles of the same launch).
+inline bool group_streams(const fd3d_ctx *const *ctx, int ns)
+{
+    if (ns < 1 || ctx[0]->tsize != 4) return false;
+    double bytes = 0.0;
+    for (int q = 0; q < ns; ++q) {
+        bytes += 12.0 * (double)ctx[q]->n[0] * (double)ctx[q]->n[1] * (double)ctx[q]->n[2] * (double)ctx[q]->tsize;
+        for (int r = 0; r < q; ++r)
+            if (shares_model(ctx[q], ctx[r])) return false;
+    }
+    return bytes > kInfinityCacheBytes;
+}
+
+// The batch's own tile shapes as one group covering every shot (counts not filled in).
+inline BatchGroup whole_batch(const fd3d_batch *b)
+{
+    BatchGroup g{};
+    g.s0 = 0;
+    g.ns = b->nshot;
+    g.tx = b->tile_x;
+    g.ty = b->tile_y;
+    g.tx2 = b->tile2_x;
+    g.ty2 = b->tile2_y;
+    g.ntp = group_streams(b->ctx.data(), b->nshot);
+    return g;
+}
+
+// Tile map of one shot of a launch, and whether it uses the launch's second tile shape
+// (when that covers its rows with fewer idle columns).
+inline TileMap shot_tiles(const BatchGroup &b, const fd3d_ctx *c, int &alt)
+{
+    int tx = b.tx, ty = b.ty;
+    alt = 0;
+    if (b.tx2 > 0) {
+        const int pad1 = (c->n[0] + tx - 1) / tx * tx, pad2 = (c->n[0] + b.tx2 - 1) / b.tx2 * b.tx2;
+        if (pad2 < pad1) {
+            alt = 1;
+            tx = b.tx2;
+            ty = b.ty2;
+        }
+    }
+    TileMap tm;
+    tm.ntx = (c->n[0] + tx - 1) / tx;
+    tm.nty = (c->n[1] + ty - 1) / ty;
+    tm.zc = c->auto_kernel && b.zc > 0 ? sweep_depth(c, b.zc) : c->zchunk;
+    tm.nzc = (c->n[2] + tm.zc - 1) / tm.zc;
+    return tm;
+}
+
+// Sweeps of a launch over ns shots of which some have no kernel selected: their common depth,
+// and unless the batch's tile shapes are selected, the launch's shape (choose_sweep).
+template <typename C> void fit_sweeps(BatchGroup &g, int ns, bool tiles_set, C &&shot)
+{
+    bool any = false;
+    for (int q = 0; q < ns; ++q) any = any || shot(q)->auto_kernel;
+    if (!any) return;
+    int zc = 0;
+    if (tiles_set) {
+        auto cols = [&](int q) {
+            int alt = 0;
+            const TileMap tm = shot_tiles(g, shot(q), alt);
+            return (long)tm.ntx * tm.nty;
+        };
+        if (launch_depth(ns, shot, cols, g.tx * g.ty, zc) < 1e300) g.zc = zc;
+        return;
+    }
+    const Sweep s = choose_sweep(ns, shot);
+    if (s.zc == 0) return;
+    g.tx = s.tx;
+    g.ty = s.ty;
+    g.tx2 = g.ty2 = 0;
+    g.zc = s.zc;
+}
+
+// Whether a launch over these shots runs the row kernels: when neither the batch has tile shapes
+// selected nor a shot a tile or fused kernel, and the arrays of all shots (`arrays` each) together
+// stay in the Infinity Cache (kernels_of).  In lockstep, us per step, rows / best tile sweep (with the depth
+// of one round), forward and gradient: six shots of 40 x 50 x 60 30.0 / 31.6 and 112.9 / 133.6,
+// eight of 64^3 46.7 / 50.6 and 208.7 / 212.1, four of 96 x 80 x 72 (106 MB) 54.1 / 54.3 and 244.2
+// / 244.3, four of 128 x 96 x 80 (189 MB) 71.5 / 79.7 and 342.3 / 348.2.
+inline bool batch_rows(bool tiles_set, const fd3d_ctx *const *ctx, int ns, int arrays)
+{
+    if (tiles_set) return false;
+    double bytes = 0.0;
+    if (ns == 1 && arrays == kForwardArrays) return kernels_of(ctx[0], arrays) == Kern::rows;
+    for (int q = 0; q < ns; ++q) {
+        const fd3d_ctx *c = ctx[q];
+        if (!rows_ok(c) || (!c->auto_kernel && c->variant != FD3D_KERNEL_CELL)) return false;
+        bytes += (double)arrays * c->n[0] * c->n[1] * c->n[2] * c->tsize;
+    }
+    return bytes <= (ctx[0]->tsize == 8 ? kRowBytes64 : kRowBytes32);
+}
+
+// Where the batch workspace holds the shots' row maps.
+inline const ShotRows *batch_row_maps(const fd3d_batch *b) { return (const ShotRows *)(b->ws + b->off_rows); }
+
+// Working set of one shot in the step loop: nine fields and the three model arrays.
+inline size_t shot_footprint(const fd3d_ctx *c) { return (size_t)12 * c->n[0] * c->n[1] * c->n[2] * c->tsize; }
+
+// Groups of the batch's schedule and their kernels: rows (batch_rows) or sweeps.  The sweeps of a
+// cache-blocked group whose shots all have the tile kernel selected with one shape of their own use
+// that shape (each shot's tuned kernel); the others the batch's selected shapes, or without those
+// what fits the shots with nothing selected (fit_sweeps).
+inline void make_groups(fd3d_batch *b)
+{
+    b->groups.clear();
+    b->order.resize(b->nshot);
+    for (int s = 0; s < b->nshot; ++s) b->order[s] = s;
+    BatchGroup all = whole_batch(b);
+    // with neither schedule nor tile shapes selected, groups that stay in the Infinity Cache
+    // (one shot per group where a shot alone exceeds it): three shots of 128^3 118.4 us per step
+    // against 134 in lockstep, two each of 128^3, 192 x 192 x 128 and 256 x 256 x 128 584 against 752
+    const size_t budget = b->sched_set || b->tiles_set ? b->group_bytes : (size_t)kRowBytes32;
+    if (budget == 0) {
+        if (batch_rows(b->tiles_set, b->ctx.data(), b->nshot, kForwardArrays)) all.rows = batch_row_maps(b);
+        else fit_sweeps(all, b->nshot, b->tiles_set, [&](int q) { return b->ctx[q]; });
+        b->groups.push_back(all);
+        return;
+    }
+    std::stable_sort(b->order.begin(), b->order.end(),
+                     [&](int x, int y) { return shot_footprint(b->ctx[x]) < shot_footprint(b->ctx[y]); });
+    auto ctx_at = [&](int p) { return b->ctx[b->order[p]]; };
+    int s = 0;
+    while (s < b->nshot) {
+        BatchGroup g = all;
+        g.s0 = s;
+        size_t bytes = shot_footprint(ctx_at(s));
+        int e = s + 1;
+        while (e < b->nshot && bytes + shot_footprint(ctx_at(e)) <= budget) bytes += shot_footprint(ctx_at(e++));
+        g.ns = e - s;
+        std::vector<const fd3d_ctx *> members;
+        for (int q = s; q < e; ++q) members.push_back(ctx_at(q));
+        g.ntp = group_streams(members.data(), g.ns);
+        if (batch_rows(b->tiles_set, members.data(), g.ns, kForwardArrays)) g.rows = batch_row_maps(b) + g.s0;
+        const fd3d_ctx *c0 = ctx_at(s);
+        auto tiled = [](const fd3d_ctx *c) { return c->variant == FD3D_KERNEL_TILE && !c->auto_kernel; };
+        bool same = tiled(c0);
+        for (int q = s + 1; q < e && same; ++q)
+            same = tiled(ctx_at(q)) && ctx_at(q)->tile_x == c0->tile_x && ctx_at(q)->tile_y == c0->tile_y;
+        if (same && tile_supported(b->tsize, c0->tile_x, c0->tile_y)) {
+            g.tx = c0->tile_x;
+            g.ty = c0->tile_y;
+            g.tx2 = g.ty2 = 0;
+        }
+        if (!g.rows) fit_sweeps(g, g.ns, b->tiles_set, [&](int q) { return ctx_at(s + q); });
+        b->groups.push_back(g);
+        s = e;
+    }
+}
+
+} // namespace fd3d

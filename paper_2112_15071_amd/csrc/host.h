@@ -6,6 +6,7 @@
 //   forward.hip   the step loop (Sec. 2.2 update order), kernel selection and its tuner
 //   gradient.hip  checkpointed discrete adjoint and the FWI gradient
 //   batch.hip     batches of shots, persistent launches, graphs, the batched gradient
+//                 (batch_plan.h: which kernels its launches run, in which order)
 //   born.hip      tangent-linear (Born) forward
 #pragma once
 

@@ -1,8 +1,11 @@
 // Prints what the library's host rules choose; built and read by test_host_rules_cpu.py.
 // One question per line of stdin: "sweep <tsize> <coarse> <nx ny nz> ..." asks for the tile
 // shape and depth of a launch over the grids, "rows <tsize> <coarse> <nx ny nz> [<receiver items> 1 1]" whether
-// the row kernels take a grid, the map of their launch and its grid of blocks.
-#include "host.h"
+// the row kernels take a grid, the map of their launch and its grid of blocks,
+// "groups <tsize> 0 <tile_x> <tile_y> <group MiB> {<nx ny nz> <kernel> 0 0}..." the groups of a batch:
+// tile_x 0: no tile shapes selected, group MiB -1: no schedule, kernel: -1 none or FD3D_KERNEL_*
+// (tiles of 64 x 16); answers shots, rows, tile_x, tile_y of each group.
+#include "batch_plan.h"
 
 #include <cstdio>
 #include <iostream>
@@ -29,11 +32,39 @@ int main()
         int ts, cm, nx, ny, nz;
         in >> what >> ts >> cm;
         std::vector<fd3d_ctx> g;
-        while (in >> nx >> ny >> nz) g.push_back(grid(nx, ny, nz, ts, cm));
+        int tx = 0, ty = 0, mib = 0;
+        if (what == "groups") in >> tx >> ty >> mib;
+        while (in >> nx >> ny >> nz) {
+            g.push_back(grid(nx, ny, nz, ts, cm));
+            if (what != "groups") continue;
+            int kernel, a, b;
+            in >> kernel >> a >> b;
+            fd3d_ctx &c = g.back();
+            c.auto_kernel = kernel < 0;
+            c.variant = kernel;
+            c.tile_x = 64;
+            c.tile_y = 16;
+            c.zchunk = 32;
+        }
         if (what == "sweep") {
             const fd3d::Sweep s = fd3d::choose_sweep((int)g.size(), [&](int q) { return &g[q]; });
             std::printf("%d %d", s.tx, s.ty);
             for (auto &c : g) std::printf(" %d", s.zc ? fd3d::sweep_depth(&c, s.zc) : 0);
+            std::printf("\n");
+        } else if (what == "groups") {
+            fd3d_batch b{};
+            char ws = 0;
+            b.nshot = (int)g.size();
+            for (auto &c : g) b.ctx.push_back(&c);
+            b.tsize = ts;
+            b.ws = &ws;  // row maps: an address to compare with null
+            b.tile_x = tx ? tx : 64;
+            b.tile_y = tx ? ty : 8;
+            b.tiles_set = tx > 0;
+            b.sched_set = mib >= 0;
+            b.group_bytes = mib > 0 ? (size_t)mib << 20 : 0;
+            fd3d::make_groups(&b);
+            for (const fd3d::BatchGroup &r : b.groups) std::printf("%d %d %d %d ", r.ns, (int)(r.rows != nullptr), r.tx, r.ty);
             std::printf("\n");
         } else if (what == "rows") {
             const fd3d::RowMap r = fd3d::row_map(&g[0]);

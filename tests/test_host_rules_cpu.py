@@ -98,3 +98,28 @@ def test_row_launches_fit_the_grid_of_blocks(ask):
     per = 8 * 16 * 256
     few, most, many = ask([f"rows 4 0 64 64 64 {q} 1 1" for q in (1, per * (65535 - 8), per * (65535 - 8) + 1)])
     assert few[9:] == [8, 16, 9] and most[9:] == [8, 16, 65535] and many[9] == 0
+
+
+CELL, TILE, NONE = 0, 1, -1
+SMALL, OTHER = (64, 64, 64), (96, 80, 72)  # 12 and 25 MiB of fields and model
+
+
+def groups(ask, tiles, mib, shots, ts=4):
+    line = f"groups {ts} 0 {tiles[0]} {tiles[1]} {mib} " + " ".join("%d %d %d %d 0 0" % (*g, k) for g, k in shots)
+    r = ask([line])[0]
+    return [tuple(r[i:i + 4]) for i in range(0, len(r), 4)]
+
+
+@pytest.mark.parametrize("kernel", [NONE, CELL])
+def test_selected_batch_tiles_exclude_the_rows(ask, kernel):
+    """Row kernels only where the batch has no tile shapes selected, in lockstep (0) and in
+    groups (16 MiB: one shot each; 64: both); with shapes selected, those, except where a group's
+    shots have a tile of their own selected."""
+    shots = [(SMALL, kernel), (OTHER, kernel)]
+    for mib in (-1, 0, 16, 64):
+        assert all(rows for _, rows, _, _ in groups(ask, (0, 0), mib, shots)), mib
+        n = 2 if mib == 16 else 1
+        assert [g[1:] for g in groups(ask, (128, 8), mib, shots)] == [(0, 128, 8)] * n, mib
+    own = [(SMALL, TILE), (OTHER, kernel)]
+    assert [g[1:] for g in groups(ask, (128, 8), 16, own)] == [(0, 64, 16), (0, 128, 8)]
+    assert [g[1:] for g in groups(ask, (128, 8), 64, own)] == [(0, 128, 8)]
