@@ -365,6 +365,16 @@ typedef struct fd3d_kernel {
 int fd3d_set_kernel(fd3d_ctx *ctx, const fd3d_kernel *k);
 int fd3d_get_kernel(const fd3d_ctx *ctx, fd3d_kernel *k);
 
+/* Largest window of planes that the context's kernels address through one buffer descriptor:
+ * 1 GiB, less here (1 <= bytes <= 2^30).  Grids with larger planes run other kernels: tile
+ * sweeps need min(zchunk + 8, nz) planes in a window (9 fields side by side with interleaved
+ * rows), the cell variant min(9, nz) for its row kernels and otherwise runs kernels with a
+ * bounds test per load and 64-bit addresses, also for the gradient and the Born forward.  A
+ * low limit runs those on any grid: for tests, results are the same but for rounding of the
+ * gradient.  Any selected kernel is dropped: the default is chosen anew.  FD3D_EINVAL with a
+ * coarse medium. */
+int fd3d_limit_window(fd3d_ctx *ctx, size_t bytes);
+
 /* Autotuner: times the cell kernel and every supported tile and fused shape with z chunks
  * of 4, 8, 16, 32, 64 and 128 planes and of ceil(nz / m) planes for m = 1 .. 8 (the whole
  * depth and its even splits; fused from 8 planes; the chunks that fit the grid) for

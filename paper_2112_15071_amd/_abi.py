@@ -122,6 +122,7 @@ _SIGS = {
                              _vp, _sz, _vp], _i),
     "fd3d_batch_destroy": ([_vp], None),
     "fd3d_autotune": ([_vp, _i, ctypes.POINTER(fd3d_kernel), _dp, _vp], _i),
+    "fd3d_limit_window": ([_vp, _sz], _i),
     "fd3d_set_kernel": ([_vp, ctypes.POINTER(fd3d_kernel)], _i),
     "fd3d_get_kernel": ([_vp, ctypes.POINTER(fd3d_kernel)], _i),
     "fd3d_profile": ([_vp, _i], _i),
@@ -318,6 +319,10 @@ def fd3d_get_kernel(ctx) -> fd3d_kernel:
     k = fd3d_kernel()
     _check(_lib.fd3d_get_kernel(ctx, ctypes.byref(k)))
     return k
+
+
+def fd3d_limit_window(ctx, nbytes: int) -> None:
+    _check(_lib.fd3d_limit_window(ctx, int(nbytes)))
 
 
 def fd3d_profile(ctx, enable: bool) -> None:

@@ -128,6 +128,7 @@ struct fd3d_ctx {
     int tile_x;   // columns of a tile (64, 128, 256)
     int tile_y;   // rows of a tile (4, 8, 16)
     int zchunk;   // z planes per workgroup sweep
+    long window;  // largest buffer window (kMaxWindowBytes; less to reach larger planes' kernels)
     bool auto_kernel;  // nothing selected yet: each operation picks rows or sweeps (kernels_of)
     // gradient state: checkpoints written by fd3d_forward_ckpt into a caller workspace
     const char *grad_ws;
@@ -311,11 +312,11 @@ template <typename T, typename F> decltype(auto) with_tile(int tx, int ty, F &&f
 enum Pass { kPassVel = 0, kPassStress = 1, kPassStressA, kPassVelA, kPassStressB, kPassVelSave, kPassStressM };
 
 // Tile and fused sweeps address a window of at most zchunk + 8 planes (and at most the
-// grid's nz) through one buffer descriptor per field, of at most 1 GiB.
+// grid's nz) through one buffer descriptor per field, of at most 1 GiB (fd3d_limit_window).
 inline bool window_ok(const fd3d_ctx *c, int zc)
 {
     const long rows = c->L.rows ? kRows : 1, planes = std::min(zc + 8, c->n[2]);
-    return planes * rows * (long)c->n[0] * (long)c->n[1] * (long)c->tsize <= kMaxWindowBytes;
+    return planes * rows * (long)c->n[0] * (long)c->n[1] * (long)c->tsize <= c->window;
 }
 
 // Tile workgroups of NT threads that the device runs at once: the tile kernels' registers

@@ -421,6 +421,16 @@ bool default_tiles(fd3d_ctx *c)
     return s.zc > 0;
 }
 
+// The kernel choice of a context with nothing selected.  False for a coarse medium whose planes
+// are too large for the sweeps it needs.
+bool default_kernel(fd3d_ctx *c)
+{
+    c->auto_kernel = default_tiles(c);
+    if (!c->auto_kernel) c->variant = FD3D_KERNEL_CELL;  // planes too large for a tile sweep
+    else c->variant = kernels_of(c, kForwardArrays) == Kern::rows ? FD3D_KERNEL_CELL : FD3D_KERNEL_TILE;
+    return !coarse_on(c->opts) || c->variant == FD3D_KERNEL_TILE;
+}
+
 // fd3d_create with the choice of creating the staging event (events = false: the
 // context creates no HIP object, for the entry point that allocates nothing).
 int create_ctx(fd3d_ctx **out, int nx, int ny, int nz, const void *lam, const void *mu, const void *rho, double dx,
@@ -471,10 +481,8 @@ int create_ctx(fd3d_ctx **out, int nx, int ny, int nz, const void *lam, const vo
     c->adj_done = 0;
     c->grad_y = 0;
     c->cur = 0;
-    c->auto_kernel = default_tiles(c);
-    if (!c->auto_kernel) c->variant = FD3D_KERNEL_CELL;  // planes too large for a tile sweep
-    else c->variant = kernels_of(c, kForwardArrays) == Kern::rows ? FD3D_KERNEL_CELL : FD3D_KERNEL_TILE;
-    if (coarse_on(c->opts) && c->variant != FD3D_KERNEL_TILE) {
+    c->window = kMaxWindowBytes;
+    if (!default_kernel(c)) {
         delete c;
         return fail(FD3D_EINVAL, "planes too large for the tile kernels, which a coarse medium needs");
     }
@@ -618,6 +626,16 @@ int fd3d_get_layout(const fd3d_ctx *ctx, int *layout)
 {
     if (!ctx || !layout) return fail(FD3D_EINVAL, "ctx/layout is NULL");
     *layout = ctx->L.rows ? FD3D_LAYOUT_ROWS : FD3D_LAYOUT_SEPARATE;
+    return FD3D_OK;
+}
+
+int fd3d_limit_window(fd3d_ctx *ctx, size_t bytes)
+{
+    if (!ctx) return fail(FD3D_EINVAL, "ctx is NULL");
+    if (bytes < 1 || bytes > (size_t)kMaxWindowBytes) return fail(FD3D_EINVAL, "bytes must be in [1, 2^30]");
+    if (coarse_on(ctx->opts)) return fail(FD3D_EINVAL, "a coarse medium needs the tile kernels");
+    ctx->window = (long)bytes;
+    default_kernel(ctx);
     return FD3D_OK;
 }
 

@@ -18,6 +18,7 @@ static fd3d_ctx grid(int nx, int ny, int nz, int tsize, int coarse)
     c.n[1] = ny;
     c.n[2] = nz;
     c.tsize = tsize;
+    c.window = fd3d::kMaxWindowBytes;
     c.opts.coarse[0] = c.opts.coarse[1] = c.opts.coarse[2] = coarse;
     // the library's automatic layout (interleaved rows when the whole depth fits one window)
     c.L.rows = 9.0 * nx * ny * nz * tsize <= (double)fd3d::kMaxWindowBytes;
