@@ -354,7 +354,8 @@ typedef struct fd3d_kernel {
     int zchunk;   /* z planes swept by one workgroup, >= 4 */
 } fd3d_kernel;
 
-/* Default at create, until fd3d_set_kernel or fd3d_autotune selects one: each operation on
+/* Default at create, until fd3d_set_kernel selects one (fd3d_autotune: for the forward, which
+ * alone it times; Born and the adjoint still pick): each operation on
  * the context (forward, gradient, Born) picks the cell or the tile kernels by the size of its
  * working set (cell while that stays in the Infinity Cache), with the tile shape and sweep
  * depth that fill the chip in one to three whole rounds; fd3d_get_kernel returns what the
@@ -363,6 +364,12 @@ typedef struct fd3d_kernel {
  * every step; the state accessors always address the current copy, and the gradient's
  * segment recompute and adjoint passes use the tile kernels of the same tile shape. */
 int fd3d_set_kernel(fd3d_ctx *ctx, const fd3d_kernel *k);
+
+/* A kernel that fd3d_autotune found for this grid, on another context or earlier (*best or
+ * fd3d_get_kernel after it): as fd3d_set_kernel for the forward, while the other operations
+ * pick.  With the cell variant k's tile shape and zchunk are those of the fastest sweep, for
+ * what runs sweeps all the same. */
+int fd3d_set_tuned(fd3d_ctx *ctx, const fd3d_kernel *k);
 int fd3d_get_kernel(const fd3d_ctx *ctx, fd3d_kernel *k);
 
 /* Largest window of planes that the context's kernels address through one buffer descriptor:

@@ -122,6 +122,7 @@ _SIGS = {
                              _vp, _sz, _vp], _i),
     "fd3d_batch_destroy": ([_vp], None),
     "fd3d_autotune": ([_vp, _i, ctypes.POINTER(fd3d_kernel), _dp, _vp], _i),
+    "fd3d_set_tuned": ([_vp, ctypes.POINTER(fd3d_kernel)], _i),
     "fd3d_limit_window": ([_vp, _sz], _i),
     "fd3d_set_kernel": ([_vp, ctypes.POINTER(fd3d_kernel)], _i),
     "fd3d_get_kernel": ([_vp, ctypes.POINTER(fd3d_kernel)], _i),
@@ -313,6 +314,10 @@ def fd3d_autotune(ctx, steps: int, stream):
 
 def fd3d_set_kernel(ctx, k: fd3d_kernel) -> None:
     _check(_lib.fd3d_set_kernel(ctx, ctypes.byref(k)))
+
+
+def fd3d_set_tuned(ctx, k: fd3d_kernel) -> None:
+    _check(_lib.fd3d_set_tuned(ctx, ctypes.byref(k)))
 
 
 def fd3d_get_kernel(ctx) -> fd3d_kernel:

@@ -56,8 +56,7 @@ class BatchSimulator:
             if key not in seen:
                 seen[key] = sim.autotune(steps, cache)
             else:
-                e = seen[key]
-                sim.set_kernel(e["variant"], e["tile_y"], e["zchunk"], e["tile_x"])
+                sim.set_tuned(seen[key])
         best = _abi.fd3d_batch_autotune(self._b, steps, _stream())
         best["per_shape"] = {f"{k[0]}": v for k, v in seen.items()}
         return best

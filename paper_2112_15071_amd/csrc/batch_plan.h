@@ -154,7 +154,7 @@ inline bool batch_rows(bool tiles_set, const fd3d_ctx *const *ctx, int ns, int a
     if (ns == 1 && arrays == kForwardArrays) return kernels_of(ctx[0], arrays) == Kern::rows;
     for (int q = 0; q < ns; ++q) {
         const fd3d_ctx *c = ctx[q];
-        if (!rows_ok(c) || (!c->auto_kernel && c->variant != FD3D_KERNEL_CELL)) return false;
+        if (!rows_ok(c) || (!unselected(c, arrays) && c->variant != FD3D_KERNEL_CELL)) return false;
         bytes += (double)arrays * c->n[0] * c->n[1] * c->n[2] * c->tsize;
     }
     return bytes <= (ctx[0]->tsize == 8 ? kRowBytes64 : kRowBytes32);

@@ -277,12 +277,28 @@ int fd3d_set_kernel(fd3d_ctx *ctx, const fd3d_kernel *k)
     if (k->variant != FD3D_KERNEL_CELL && !window_ok(ctx, k->zchunk))
         return fail(FD3D_EINVAL, "zchunk too large: a sweep's window (zchunk + 8 planes, at most nz) must fit in 1 GiB");
     ctx->variant = k->variant;
-    ctx->auto_kernel = false;
+    ctx->auto_kernel = ctx->tuned = false;
     if (k->variant != FD3D_KERNEL_CELL) {
         ctx->tile_x = k->tile_x;
         ctx->tile_y = k->tile_y;
     }
     ctx->zchunk = k->zchunk;
+    return FD3D_OK;
+}
+
+int fd3d_set_tuned(fd3d_ctx *ctx, const fd3d_kernel *k)
+{
+    const int rc = fd3d_set_kernel(ctx, k);
+    if (rc) return rc;
+    if (k->variant == FD3D_KERNEL_CELL) {  // the sweeps' tile beside it
+        if (tile_supported(ctx->tsize, k->tile_x, k->tile_y) && window_ok(ctx, k->zchunk)) {
+            ctx->tile_x = k->tile_x;
+            ctx->tile_y = k->tile_y;
+        } else {
+            default_tiles(ctx);
+        }
+    }
+    ctx->tuned = window_ok(ctx, ctx->zchunk);
     return FD3D_OK;
 }
 
@@ -317,7 +333,7 @@ int fd3d_autotune(fd3d_ctx *ctx, int steps, fd3d_kernel *best, double *best_ms, 
     std::sort(chunks.begin(), chunks.end());
     const int nt_save = ctx->nt;
     const fd3d_kernel keep = {ctx->variant, ctx->tile_x, ctx->tile_y, ctx->zchunk};
-    const bool keep_auto = ctx->auto_kernel;
+    const bool keep_auto = ctx->auto_kernel, keep_tuned = ctx->tuned;
     ctx->auto_kernel = false;
     fd3d_kernel win = keep, win_tile = keep;  // the best of all, and of the tile sweeps
     double win_ms = 1e300, tile_ms = 1e300;
@@ -373,8 +389,8 @@ int fd3d_autotune(fd3d_ctx *ctx, int steps, fd3d_kernel *best, double *best_ms, 
         }
         if (rc) break;
     }
-    // the cell kernels have no tile: the context keeps the best sweep's beside them, which
-    // batches use where they run sweeps
+    // the cell kernels have no tile: the context keeps the best sweep's beside them, for what runs
+    // sweeps all the same (the operations not timed here, batches)
     if (win.variant == FD3D_KERNEL_CELL && tile_ms < 1e300)
         win = fd3d_kernel{FD3D_KERNEL_CELL, win_tile.tile_x, win_tile.tile_y, win_tile.zchunk};
     ctx->nt = nt_save;
@@ -386,6 +402,7 @@ int fd3d_autotune(fd3d_ctx *ctx, int steps, fd3d_kernel *best, double *best_ms, 
     ctx->tile_x = use.tile_x;
     ctx->tile_y = use.tile_y;
     ctx->zchunk = use.zchunk;
+    ctx->tuned = rc ? keep_tuned : window_ok(ctx, ctx->zchunk);
     if (rc) return rc;
     zero_fields_any(ctx, st);
     if (best) *best = win;

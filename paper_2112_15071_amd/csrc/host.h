@@ -130,6 +130,7 @@ struct fd3d_ctx {
     int zchunk;   // z planes per workgroup sweep
     long window;  // largest buffer window (kMaxWindowBytes; less to reach larger planes' kernels)
     bool auto_kernel;  // nothing selected yet: each operation picks rows or sweeps (kernels_of)
+    bool tuned;        // the variant is the forward tuner's: the other operations still pick
     // gradient state: checkpoints written by fd3d_forward_ckpt into a caller workspace
     const char *grad_ws;
     int grad_k;
@@ -476,8 +477,8 @@ inline bool rows_ok(const fd3d_ctx *c)
 inline bool cells_ok(const fd3d_ctx *c) { return c->n[2] <= kMaxGridYZ && (c->n[1] + 3) / 4 <= kMaxGridYZ; }
 
 // Kernels of an operation that steps `arrays` cell-sized arrays: rows, tile sweeps, or the
-// kernels with a bounds test per load (cells).  A selected variant decides; with nothing
-// selected, the rows run while the arrays stay in the Infinity Cache, and else the sweeps.
+// kernels with a bounds test per load (cells).  A selected variant decides, one that the tuner
+// found for the forward, which alone it timed; with nothing selected, the rows run while the arrays stay in the Infinity Cache, and else the sweeps.
 // Measured on both sides of the limit (FP32, MI355X, us per step, rows / best tile sweep): the
 // forward's 12 arrays at 192 x 192 x 128 (226 MB) 89 / 94 and 256 x 256 x 96 (302 MB) 156 / 133;
 // Born's 24 at 128^3 (201 MB) 74 / 94 and 192 x 160 x 128 (377 MB) 210 / 185; the adjoint's 29 at
@@ -487,13 +488,24 @@ inline bool cells_ok(const fd3d_ctx *c) { return c->n[2] <= kMaxGridYZ && (c->n[
 constexpr int kForwardArrays = 12, kBornArrays = 24, kAdjointArrays = 29;
 constexpr double kRowBytes32 = 230.0 * 1024 * 1024, kRowBytes64 = 64.0 * 1024 * 1024;
 enum class Kern { rows, tiles, cells };
+inline bool unselected(const fd3d_ctx *c, int arrays) { return c->auto_kernel || (c->tuned && arrays != kForwardArrays); }
 inline Kern kernels_of(const fd3d_ctx *c, int arrays)
 {
-    if (!c->auto_kernel)
+    if (!unselected(c, arrays))
         return c->variant != FD3D_KERNEL_CELL ? Kern::tiles : rows_ok(c) ? Kern::rows : Kern::cells;
     if (coarse_on(c->opts)) return Kern::tiles;
     const double bytes = (double)arrays * c->n[0] * c->n[1] * c->n[2] * c->tsize;
     return bytes <= (c->tsize == 8 ? kRowBytes64 : kRowBytes32) && rows_ok(c) ? Kern::rows : Kern::tiles;
+}
+
+// Default tile shape and sweep depth (choose_sweep).  False when no sweep fits one window.
+inline bool default_tiles(fd3d_ctx *c)
+{
+    const Sweep s = choose_sweep(1, [c](int) { return c; });
+    c->tile_x = s.tx;
+    c->tile_y = s.ty;
+    c->zchunk = s.zc > 0 ? sweep_depth(c, s.zc) : 4;
+    return s.zc > 0;
 }
 
 // Cache policy of a context's single-grid tile launches: the model arrays and the

@@ -411,20 +411,11 @@ int fd3d_workspace_bytes(int nx, int ny, int nz, const fd3d_opts *opts, size_t *
 
 namespace {
 
-// Default tile shape and sweep depth (choose_sweep).  False when no sweep fits one window.
-bool default_tiles(fd3d_ctx *c)
-{
-    const Sweep s = choose_sweep(1, [c](int) { return c; });
-    c->tile_x = s.tx;
-    c->tile_y = s.ty;
-    c->zchunk = s.zc > 0 ? sweep_depth(c, s.zc) : 4;
-    return s.zc > 0;
-}
-
 // The kernel choice of a context with nothing selected.  False for a coarse medium whose planes
 // are too large for the sweeps it needs.
 bool default_kernel(fd3d_ctx *c)
 {
+    c->tuned = false;
     c->auto_kernel = default_tiles(c);
     if (!c->auto_kernel) c->variant = FD3D_KERNEL_CELL;  // planes too large for a tile sweep
     else c->variant = kernels_of(c, kForwardArrays) == Kern::rows ? FD3D_KERNEL_CELL : FD3D_KERNEL_TILE;

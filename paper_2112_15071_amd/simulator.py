@@ -199,10 +199,19 @@ class Simulator:
         zchunk planes) or "fused" (velocity and stress of a step in one sweep, tile_x = 64).
         Until one is selected or tuned, each operation takes "cell" while its arrays stay
         in the last-level cache and "tile" sweeps otherwise."""
+        _abi.fd3d_set_kernel(self._ctx, self._kernel(variant, tile_y, zchunk, tile_x))
+
+    @classmethod
+    def _kernel(cls, variant: str, tile_y: int, zchunk: int, tile_x: int) -> _abi.fd3d_kernel:
         k = _abi.fd3d_kernel()
-        k.variant = self._VARIANTS[variant]
+        k.variant = cls._VARIANTS[variant]
         k.tile_x, k.tile_y, k.zchunk = int(tile_x), int(tile_y), int(zchunk)
-        _abi.fd3d_set_kernel(self._ctx, k)
+        return k
+
+    def set_tuned(self, e: dict) -> None:
+        """Take over a kernel that ``autotune`` found for this grid (its result, or ``kernel()``
+        of a tuned simulator): for the forward, as the tuner that timed it."""
+        _abi.fd3d_set_tuned(self._ctx, self._kernel(e["variant"], e["tile_y"], e["zchunk"], e["tile_x"]))
 
     def layout(self) -> str:
         """The field storage the library chose: "separate" or "rows"."""
@@ -214,8 +223,9 @@ class Simulator:
         return {"variant": name, "tile_x": k.tile_x, "tile_y": k.tile_y, "zchunk": k.zchunk}
 
     def autotune(self, steps: int = 20, cache: bool = True) -> dict:
-        """Pick the fastest kernel variant, tile shape and z chunk for this grid (fd3d_autotune), with a
-        JSON cache keyed by grid shape, dtype, free surface and device (CU count, memory size)
+        """Pick the fastest kernel variant, tile shape and z chunk of the forward for this grid
+        (fd3d_autotune; Born and the gradient keep the library's choice between rows and sweeps),
+        with a JSON cache keyed by grid shape, dtype, free surface and device (CU count, memory size)
         ($FD3D_AUTOTUNE_CACHE, default ~/.cache/fd3d/autotune.json).  Zeroes the state."""
         nx, ny, nz = self.shape
         props = torch.cuda.get_device_properties(self.device)
@@ -232,7 +242,7 @@ class Simulator:
                 table = {}
         if cache and key in table and "variant" in table[key]:
             e = table[key]
-            self.set_kernel(e["variant"], e["tile_y"], e["zchunk"], e["tile_x"])
+            self.set_tuned(e)
             return dict(e, cached=True)
         _, ms = _abi.fd3d_autotune(self._ctx, steps, _stream())
         e = dict(self.kernel(), ms_per_step=ms)

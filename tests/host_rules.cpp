@@ -5,6 +5,8 @@
 // "groups <tsize> 0 <tile_x> <tile_y> <group MiB> {<nx ny nz> <kernel> 0 0}..." the groups of a batch:
 // tile_x 0: no tile shapes selected, group MiB -1: no schedule, kernel: -1 none or FD3D_KERNEL_*
 // (tiles of 64 x 16); answers shots, rows, tile_x, tile_y of each group.
+// "kern <tsize> <coarse> <tuned> 0 0 <nx ny nz> <kernel> 0 0" what forward, Born and adjoint run
+// (0 rows, 1 sweeps, 2 kernels with a bounds test per load).
 #include "batch_plan.h"
 
 #include <cstdio>
@@ -34,10 +36,11 @@ int main()
         in >> what >> ts >> cm;
         std::vector<fd3d_ctx> g;
         int tx = 0, ty = 0, mib = 0;
-        if (what == "groups") in >> tx >> ty >> mib;
+        const bool select = what == "groups" || what == "kern";
+        if (select) in >> tx >> ty >> mib;
         while (in >> nx >> ny >> nz) {
             g.push_back(grid(nx, ny, nz, ts, cm));
-            if (what != "groups") continue;
+            if (!select) continue;
             int kernel, a, b;
             in >> kernel >> a >> b;
             fd3d_ctx &c = g.back();
@@ -66,6 +69,11 @@ int main()
             b.group_bytes = mib > 0 ? (size_t)mib << 20 : 0;
             fd3d::make_groups(&b);
             for (const fd3d::BatchGroup &r : b.groups) std::printf("%d %d %d %d ", r.ns, (int)(r.rows != nullptr), r.tx, r.ty);
+            std::printf("\n");
+        } else if (what == "kern") {
+            g[0].tuned = tx != 0;
+            for (int a : {fd3d::kForwardArrays, fd3d::kBornArrays, fd3d::kAdjointArrays})
+                std::printf("%d ", (int)fd3d::kernels_of(&g[0], a));
             std::printf("\n");
         } else if (what == "rows") {
             const fd3d::RowMap r = fd3d::row_map(&g[0]);

@@ -1,0 +1,106 @@
+"""Which kernels a call runs (from a trace of its launches) after the tuners and the calls that
+carry a kernel choice from one simulator to another.  All kernels give the same bits, so only the
+launches can tell."""
+from __future__ import annotations
+
+import json
+import re
+
+import numpy as np
+import pytest
+import torch
+
+import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+H, DT, NT = 10.0, 5e-4, 3
+SMALL = (40, 36, 32)      # every operation's arrays stay in the cache: rows
+MIDDLE = (192, 160, 128)  # the forward's do (180 MiB), Born's (360) and the adjoint's (435) do not
+
+
+def launched(fn) -> set:
+    """Names of the library's kernels that fn launches."""
+    from torch.profiler import ProfilerActivity, profile
+
+    fn()
+    torch.cuda.synchronize()
+    with profile(activities=[ProfilerActivity.CUDA]) as p:
+        fn()
+        torch.cuda.synchronize()
+    names = {m.group(1) for e in p.key_averages() for m in [re.search(r"fd3d::(\w+)<", e.key)] if m}
+    assert names, "no launch was recorded"
+    return names
+
+
+def simulator(shape, nt=NT, **kw):
+    from paper_2112_15071_amd import Simulator
+
+    nx, ny, nz = shape
+    lam = torch.full((nz, ny, nx), 7.5e9, device="cuda")
+    return Simulator(lam, lam, torch.full_like(lam, 2500.0), H, DT, nt, sponge=3, **kw)
+
+
+def shot(shape, nt=NT):
+    mid = np.array(shape) / 2 + 0.3
+    return dict(src_pos=tuple(mid), moment=W.explosion(1e15), wavelet=np.ones(nt), rec_pos=[mid + 2, mid - 3])
+
+
+def gradient(sim):
+    obs = torch.zeros((2, 3, sim.nt), device="cuda")
+    g = [torch.zeros_like(sim.lam) for _ in range(3)]
+    gws = sim.grad_workspace(2)
+    return lambda: sim.gradient(gws, obs, *g, **shot(sim.shape, sim.nt))
+
+
+def born(sim):
+    return lambda: sim.born(sim.lam, sim.lam, sim.rho, **shot(sim.shape, sim.nt))
+
+
+def forward(sim):
+    return lambda: sim.forward(**shot(sim.shape, sim.nt))
+
+
+ROWS = dict(forward={"vel_row", "stress_row"}, gradient={"vel_row_io", "stress_row_io"}, born={"vel_row_io", "stress_row_io"})
+SWEEPS = dict(forward={"vel_tile", "stress_tile"}, gradient={"vel_tile_adj", "stress_tile_adj"},
+              born={"vel_tile_adj", "stress_tile_born"})
+
+
+def runs(sim, what) -> str:
+    names = launched(dict(forward=forward, gradient=gradient, born=born)[what](sim))
+    rows, sweeps = ROWS[what] <= names, SWEEPS[what] <= names
+    assert rows != sweeps, names
+    return "rows" if rows else "sweeps"
+
+
+@pytest.mark.parametrize("cached", [False, True])
+def test_forward_tuner_leaves_the_other_operations_alone(cached, tmp_path, monkeypatch):
+    """The forward of a tuned simulator runs the tuner's kernel; Born and the gradient, which it
+    did not time, rows or sweeps by the size of their arrays, on the simulator that was tuned and
+    (cached: the cell variant as the saved winner) on one that takes the saved result."""
+    monkeypatch.setenv("FD3D_AUTOTUNE_CACHE", str(tmp_path / "tuned.json"))
+    for shape, others in ((SMALL, "rows"), (MIDDLE, "sweeps")):
+        sim = simulator(shape)
+        sim.autotune(steps=1)
+        if cached:
+            sim.close()
+            table = json.loads((tmp_path / "tuned.json").read_text())
+            for e in table.values():
+                e["variant"] = "cell"
+            (tmp_path / "tuned.json").write_text(json.dumps(table))
+            sim = simulator(shape)
+            assert sim.autotune(steps=1)["cached"] and sim.kernel()["variant"] == "cell"
+        variant = sim.kernel()["variant"]
+        if variant != "fused":
+            assert runs(sim, "forward") == {"cell": "rows", "tile": "sweeps"}[variant], shape
+            assert runs(sim, "born") == others, shape
+        assert runs(sim, "gradient") == others, shape
+        sim.close()
+
+
+def test_selected_kernel_runs_every_operation():
+    sim = simulator(MIDDLE)
+    for kernel, want in ((("cell", 4, 8, 64), "rows"), (("tile", 4, 32, 256), "sweeps")):
+        sim.set_kernel(*kernel)
+        assert [runs(sim, w) for w in ("forward", "born", "gradient")] == [want] * 3
+    sim.close()

@@ -123,3 +123,17 @@ def test_selected_batch_tiles_exclude_the_rows(ask, kernel):
     own = [(SMALL, TILE), (OTHER, kernel)]
     assert [g[1:] for g in groups(ask, (128, 8), 16, own)] == [(0, 64, 16), (0, 128, 8)]
     assert [g[1:] for g in groups(ask, (128, 8), 64, own)] == [(0, 128, 8)]
+
+
+def test_kernels_of_an_operation(ask):
+    """With nothing selected every operation goes by the size of its arrays, with a kernel
+    selected by that, and with a tuned one only the forward by that."""
+    rows, sweeps = 0, 1
+    cases = [((64, 64, 64), NONE, 0, [rows] * 3), ((160, 150, 100), NONE, 0, [rows, rows, sweeps]),
+             ((192, 160, 128), NONE, 0, [rows, sweeps, sweeps]), ((256, 256, 256), NONE, 0, [sweeps] * 3),
+             ((192, 160, 128), CELL, 0, [rows] * 3), ((64, 64, 64), TILE, 0, [sweeps] * 3),
+             ((192, 160, 128), CELL, 1, [rows, sweeps, sweeps]), ((64, 64, 64), TILE, 1, [sweeps, rows, rows]),
+             ((256, 256, 256), CELL, 1, [rows, sweeps, sweeps]), ((160, 150, 100), CELL, 1, [rows, rows, sweeps])]
+    got = ask([f"kern 4 0 {t} 0 0 %d %d %d {k} 0 0" % g for g, k, t, _ in cases])
+    for (g, k, t, want), r in zip(cases, got):
+        assert r == want, (g, k, t)
