@@ -334,7 +334,6 @@ int fd3d_autotune(fd3d_ctx *ctx, int steps, fd3d_kernel *best, double *best_ms, 
     const int nt_save = ctx->nt;
     const fd3d_kernel keep = {ctx->variant, ctx->tile_x, ctx->tile_y, ctx->zchunk};
     const bool keep_auto = ctx->auto_kernel, keep_tuned = ctx->tuned;
-    ctx->auto_kernel = false;
     fd3d_kernel win = keep, win_tile = keep;  // the best of all, and of the tile sweeps
     double win_ms = 1e300, tile_ms = 1e300;
     hipEvent_t e0 = nullptr, e1 = nullptr;
@@ -343,6 +342,7 @@ int fd3d_autotune(fd3d_ctx *ctx, int steps, fd3d_kernel *best, double *best_ms, 
         if (e1) (void)hipEventDestroy(e1);
         return fail(FD3D_EHIP, "hipEventCreate failed");
     }
+    ctx->auto_kernel = false;
     ctx->nt = steps;
     int rc = FD3D_OK;
     for (const auto &sh : shapes) {

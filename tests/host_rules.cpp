@@ -6,7 +6,9 @@
 // tile_x 0: no tile shapes selected, group MiB -1: no schedule, kernel: -1 none or FD3D_KERNEL_*
 // (tiles of 64 x 16); answers shots, rows, tile_x, tile_y of each group.
 // "kern <tsize> <coarse> <tuned> 0 0 <nx ny nz> <kernel> 0 0" what forward, Born and adjoint run
-// (0 rows, 1 sweeps, 2 kernels with a bounds test per load).
+// (0 rows, 1 sweeps, 2 kernels with a bounds test per load).  "tuner <tsize> 0 <nx ny nz>" runs
+// fd3d_autotune where there is no device, so that it fails, and prints its return code and
+// whether the context still has nothing selected.
 #include "batch_plan.h"
 
 #include <cstdio>
@@ -75,6 +77,12 @@ int main()
             for (int a : {fd3d::kForwardArrays, fd3d::kBornArrays, fd3d::kAdjointArrays})
                 std::printf("%d ", (int)fd3d::kernels_of(&g[0], a));
             std::printf("\n");
+        } else if (what == "tuner") {
+            int n = 0;
+            if (hipGetDeviceCount(&n) == hipSuccess && n > 0) return 1;  // no workspace to run on
+            g[0].auto_kernel = true;
+            const int rc = fd3d_autotune(&g[0], 1, nullptr, nullptr, nullptr);
+            std::printf("%d %d\n", rc, (int)g[0].auto_kernel);
         } else if (what == "rows") {
             const fd3d::RowMap r = fd3d::row_map(&g[0]);
             const dim3 b = fd3d::row_grid(r, g.size() > 1 ? g[1].n[0] : 0);

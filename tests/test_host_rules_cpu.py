@@ -17,7 +17,7 @@ def ask(tmp_path_factory):
     exe = str(tmp_path_factory.mktemp("host_rules") / "host_rules")
     subprocess.run([B.HIPCC, "--offload-arch=gfx950", "--offload-host-only", "-x", "hip", "-std=c++17", "-O1", "-w",
                     "-I", os.path.join(ROOT, "include"), "-I", B.CSRC, os.path.join(ROOT, "tests", "host_rules.cpp"),
-                    "-o", exe], check=True)
+                    "-o", exe, "-x", "none", B.LIB, "-Wl,-rpath," + os.path.dirname(B.LIB)], check=True)
 
     def run(lines):
         out = subprocess.run([exe], input="\n".join(lines) + "\n", capture_output=True, text=True, check=True).stdout
@@ -137,3 +137,13 @@ def test_kernels_of_an_operation(ask):
     got = ask([f"kern 4 0 {t} 0 0 %d %d %d {k} 0 0" % g for g, k, t, _ in cases])
     for (g, k, t, want), r in zip(cases, got):
         assert r == want, (g, k, t)
+
+
+def test_failed_tuner_leaves_nothing_selected(ask):
+    """Without a device the tuner's events cannot be created: FD3D_EHIP, and the context's
+    operations still pick their kernels."""
+    import torch
+
+    if torch.cuda.is_available():
+        pytest.skip("needs a machine without a GPU")
+    assert ask(["tuner 4 0 64 64 64"]) == [[-6, 1]]
