@@ -167,8 +167,8 @@ inline const ShotRows *batch_row_maps(const fd3d_batch *b) { return (const ShotR
 inline size_t shot_footprint(const fd3d_ctx *c) { return (size_t)12 * c->n[0] * c->n[1] * c->n[2] * c->tsize; }
 
 // Groups of the batch's schedule and their kernels: rows (batch_rows) or sweeps.  The sweeps of a
-// cache-blocked group whose shots all have the tile kernel selected with one shape of their own use
-// that shape (each shot's tuned kernel); the others the batch's selected shapes, or without those
+// cache-blocked group whose shots all have the tile kernel selected, or are tuned, with one shape of
+// their own use that shape; the others the batch's selected shapes, or without those
 // what fits the shots with nothing selected (fit_sweeps).
 inline void make_groups(fd3d_batch *b)
 {
@@ -202,7 +202,9 @@ inline void make_groups(fd3d_batch *b)
         g.ntp = group_streams(members.data(), g.ns);
         if (batch_rows(b->tiles_set, members.data(), g.ns, kForwardArrays)) g.rows = batch_row_maps(b) + g.s0;
         const fd3d_ctx *c0 = ctx_at(s);
-        auto tiled = [](const fd3d_ctx *c) { return c->variant == FD3D_KERNEL_TILE && !c->auto_kernel; };
+        auto tiled = [](const fd3d_ctx *c) {
+            return !c->auto_kernel && (c->variant == FD3D_KERNEL_TILE || (c->variant == FD3D_KERNEL_CELL && c->tuned));
+        };
         bool same = tiled(c0);
         for (int q = s + 1; q < e && same; ++q)
             same = tiled(ctx_at(q)) && ctx_at(q)->tile_x == c0->tile_x && ctx_at(q)->tile_y == c0->tile_y;

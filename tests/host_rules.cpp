@@ -4,8 +4,8 @@
 // the row kernels take a grid, the map of their launch and its grid of blocks,
 // "groups <tsize> 0 <tile_x> <tile_y> <group MiB> {<nx ny nz> <kernel> 0 0}..." the groups of a batch:
 // tile_x 0: no tile shapes selected, group MiB -1: no schedule, kernel: -1 none or FD3D_KERNEL_*
-// (tiles of 64 x 16); answers shots, rows, tile_x, tile_y of each group.
-// "kern <tsize> <coarse> <tuned> 0 0 <nx ny nz> <kernel> 0 0" what forward, Born and adjoint run
+// (tiles of 64 x 16), 10 more: the tuner's; answers shots, rows, tile_x, tile_y of each group.
+// "kern <tsize> <coarse> 0 0 0 <nx ny nz> <kernel> 0 0" what forward, Born and adjoint run
 // (0 rows, 1 sweeps, 2 kernels with a bounds test per load).  "tuner <tsize> 0 <nx ny nz>" runs
 // fd3d_autotune where there is no device, so that it fails, and prints its return code and
 // whether the context still has nothing selected.
@@ -47,7 +47,8 @@ int main()
             in >> kernel >> a >> b;
             fd3d_ctx &c = g.back();
             c.auto_kernel = kernel < 0;
-            c.variant = kernel;
+            c.tuned = kernel >= 10;
+            c.variant = kernel >= 10 ? kernel - 10 : kernel;
             c.tile_x = 64;
             c.tile_y = 16;
             c.zchunk = 32;
@@ -73,7 +74,6 @@ int main()
             for (const fd3d::BatchGroup &r : b.groups) std::printf("%d %d %d %d ", r.ns, (int)(r.rows != nullptr), r.tx, r.ty);
             std::printf("\n");
         } else if (what == "kern") {
-            g[0].tuned = tx != 0;
             for (int a : {fd3d::kForwardArrays, fd3d::kBornArrays, fd3d::kAdjointArrays})
                 std::printf("%d ", (int)fd3d::kernels_of(&g[0], a));
             std::printf("\n");

@@ -100,7 +100,7 @@ def test_row_launches_fit_the_grid_of_blocks(ask):
     assert few[9:] == [8, 16, 9] and most[9:] == [8, 16, 65535] and many[9] == 0
 
 
-CELL, TILE, NONE = 0, 1, -1
+CELL, TILE, NONE, TUNED_CELL, TUNED_TILE = 0, 1, -1, 10, 11
 SMALL, OTHER = (64, 64, 64), (96, 80, 72)  # 12 and 25 MiB of fields and model
 
 
@@ -129,14 +129,14 @@ def test_kernels_of_an_operation(ask):
     """With nothing selected every operation goes by the size of its arrays, with a kernel
     selected by that, and with a tuned one only the forward by that."""
     rows, sweeps = 0, 1
-    cases = [((64, 64, 64), NONE, 0, [rows] * 3), ((160, 150, 100), NONE, 0, [rows, rows, sweeps]),
-             ((192, 160, 128), NONE, 0, [rows, sweeps, sweeps]), ((256, 256, 256), NONE, 0, [sweeps] * 3),
-             ((192, 160, 128), CELL, 0, [rows] * 3), ((64, 64, 64), TILE, 0, [sweeps] * 3),
-             ((192, 160, 128), CELL, 1, [rows, sweeps, sweeps]), ((64, 64, 64), TILE, 1, [sweeps, rows, rows]),
-             ((256, 256, 256), CELL, 1, [rows, sweeps, sweeps]), ((160, 150, 100), CELL, 1, [rows, rows, sweeps])]
-    got = ask([f"kern 4 0 {t} 0 0 %d %d %d {k} 0 0" % g for g, k, t, _ in cases])
-    for (g, k, t, want), r in zip(cases, got):
-        assert r == want, (g, k, t)
+    cases = [((64, 64, 64), NONE, [rows] * 3), ((160, 150, 100), NONE, [rows, rows, sweeps]),
+             ((192, 160, 128), NONE, [rows, sweeps, sweeps]), ((256, 256, 256), NONE, [sweeps] * 3),
+             ((192, 160, 128), CELL, [rows] * 3), ((64, 64, 64), TILE, [sweeps] * 3),
+             ((192, 160, 128), TUNED_CELL, [rows, sweeps, sweeps]), ((64, 64, 64), TUNED_TILE, [sweeps, rows, rows]),
+             ((256, 256, 256), TUNED_CELL, [rows, sweeps, sweeps]), ((160, 150, 100), TUNED_CELL, [rows, rows, sweeps])]
+    got = ask([f"kern 4 0 0 0 0 %d %d %d {k} 0 0" % g for g, k, _ in cases])
+    for (g, k, want), r in zip(cases, got):
+        assert r == want, (g, k)
 
 
 def test_failed_tuner_leaves_nothing_selected(ask):
@@ -147,3 +147,14 @@ def test_failed_tuner_leaves_nothing_selected(ask):
     if torch.cuda.is_available():
         pytest.skip("needs a machine without a GPU")
     assert ask(["tuner 4 0 64 64 64"]) == [[-6, 1]]
+
+
+def test_groups_use_the_tuned_sweep(ask):
+    """Shots tuned to the cell variant keep the fastest sweep's tile (64 x 16 here) beside it; a
+    group of them that exceeds the cache, and so runs sweeps, uses it, as one of shots tuned to
+    that tile does; shots with the cell variant merely selected have no tile of their own."""
+    big = (160, 150, 140)  # 154 MiB
+    for kernel, tile in ((TUNED_CELL, (64, 16)), (TUNED_TILE, (64, 16)), (CELL, (64, 8))):
+        assert groups(ask, (0, 0), 400, [(big, kernel), (big, kernel)]) == [(2, 0, *tile)], kernel
+    assert groups(ask, (0, 0), 400, [(big, TUNED_CELL), (big, TUNED_TILE)]) == [(2, 0, 64, 16)]
+    assert [g[1] for g in groups(ask, (0, 0), 160, [(big, TUNED_CELL)] * 2)] == [1, 1]
