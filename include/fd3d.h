@@ -370,6 +370,14 @@ int fd3d_set_kernel(fd3d_ctx *ctx, const fd3d_kernel *k);
  * pick.  With the cell variant k's tile shape and zchunk are those of the fastest sweep, for
  * what runs sweeps all the same. */
 int fd3d_set_tuned(fd3d_ctx *ctx, const fd3d_kernel *k);
+
+/* The kernel choice of another context over a grid of the same size, dtype, field layout and
+ * kind of medium: selected, tuned, or none yet.  (fd3d_get_kernel and fd3d_set_kernel would
+ * select what only the forward runs.)  FD3D_EINVAL for other contexts. */
+int fd3d_copy_kernel(fd3d_ctx *ctx, const fd3d_ctx *from);
+
+/* The depth of the context's sweeps alone (>= 4, within one window): selects no kernel. */
+int fd3d_set_zchunk(fd3d_ctx *ctx, int zchunk);
 int fd3d_get_kernel(const fd3d_ctx *ctx, fd3d_kernel *k);
 
 /* Largest window of planes that the context's kernels address through one buffer descriptor:

@@ -122,6 +122,8 @@ _SIGS = {
                              _vp, _sz, _vp], _i),
     "fd3d_batch_destroy": ([_vp], None),
     "fd3d_autotune": ([_vp, _i, ctypes.POINTER(fd3d_kernel), _dp, _vp], _i),
+    "fd3d_copy_kernel": ([_vp, _vp], _i),
+    "fd3d_set_zchunk": ([_vp, _i], _i),
     "fd3d_set_tuned": ([_vp, ctypes.POINTER(fd3d_kernel)], _i),
     "fd3d_limit_window": ([_vp, _sz], _i),
     "fd3d_set_kernel": ([_vp, ctypes.POINTER(fd3d_kernel)], _i),
@@ -318,6 +320,14 @@ def fd3d_set_kernel(ctx, k: fd3d_kernel) -> None:
 
 def fd3d_set_tuned(ctx, k: fd3d_kernel) -> None:
     _check(_lib.fd3d_set_tuned(ctx, ctypes.byref(k)))
+
+
+def fd3d_copy_kernel(ctx, from_ctx) -> None:
+    _check(_lib.fd3d_copy_kernel(ctx, from_ctx))
+
+
+def fd3d_set_zchunk(ctx, zchunk: int) -> None:
+    _check(_lib.fd3d_set_zchunk(ctx, int(zchunk)))
 
 
 def fd3d_get_kernel(ctx) -> fd3d_kernel:

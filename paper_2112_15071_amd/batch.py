@@ -70,8 +70,7 @@ class BatchSimulator:
     @staticmethod
     def _set_zchunk(sims, zc: int) -> None:
         for sim in sims:
-            k = sim.kernel()
-            sim.set_kernel(k["variant"], k["tile_y"], zc if zc > 0 else sim.shape[2], k["tile_x"])
+            _abi.fd3d_set_zchunk(sim.ctx, zc if zc > 0 else sim.shape[2])
 
     def autotune_gradient(self, shots: List[Dict], steps: int = 40, ckpt_every: int = 20, candidates=None) -> dict:
         """Pick the tile shape and z chunk of the batched gradient: times the batched

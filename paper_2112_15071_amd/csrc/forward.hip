@@ -302,6 +302,36 @@ int fd3d_set_tuned(fd3d_ctx *ctx, const fd3d_kernel *k)
     return FD3D_OK;
 }
 
+int fd3d_copy_kernel(fd3d_ctx *ctx, const fd3d_ctx *from)
+{
+    if (!ctx || !from) return fail(FD3D_EINVAL, "ctx/from is NULL");
+    for (int a = 0; a < 3; ++a)
+        if (ctx->n[a] != from->n[a]) return fail(FD3D_EINVAL, "contexts differ in grid size");
+    if (ctx->tsize != from->tsize || ctx->L.rows != from->L.rows || coarse_on(ctx->opts) != coarse_on(from->opts))
+        return fail(FD3D_EINVAL, "contexts differ in dtype, field layout or medium");
+    if (from->variant == FD3D_KERNEL_FUSED && !fused_supported(ctx, from->tile_x, from->tile_y))
+        return fail(FD3D_EINVAL, "the fused kernel does not run on this context");
+    ctx->variant = from->variant;
+    ctx->tile_x = from->tile_x;
+    ctx->tile_y = from->tile_y;
+    ctx->zchunk = from->zchunk;
+    ctx->window = from->window;
+    ctx->auto_kernel = from->auto_kernel;
+    ctx->tuned = from->tuned;
+    return FD3D_OK;
+}
+
+int fd3d_set_zchunk(fd3d_ctx *ctx, int zchunk)
+{
+    if (!ctx) return fail(FD3D_EINVAL, "ctx is NULL");
+    if (zchunk < 4) return fail(FD3D_EINVAL, "zchunk must be >= 4");
+    const bool cell = ctx->variant == FD3D_KERNEL_CELL && !ctx->auto_kernel && !ctx->tuned;  // runs no sweep
+    if (!cell && !window_ok(ctx, zchunk))
+        return fail(FD3D_EINVAL, "zchunk too large: a sweep's window (zchunk + 8 planes, at most nz) must fit in 1 GiB");
+    ctx->zchunk = zchunk;
+    return FD3D_OK;
+}
+
 int fd3d_get_kernel(const fd3d_ctx *ctx, fd3d_kernel *k)
 {
     if (!ctx || !k) return fail(FD3D_EINVAL, "ctx/k is NULL");

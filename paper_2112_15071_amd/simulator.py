@@ -264,15 +264,14 @@ class Simulator:
 
     def like(self, nt: int) -> "Simulator":
         """A new context over the same model arrays, spacing and options, with nt steps and
-        this context's kernel configuration."""
+        this context's kernel choice (selected, tuned, or the library's)."""
         o = self.opts
         sim = Simulator(self.lam, self.mu, self.rho, self.spacing, self.dt, nt, dtype=self.dtype,
                         sponge=[o.sponge[f] for f in range(6)], sponge_alpha=o.sponge_alpha,
                         free_surface=bool(o.free_surface), check_finite=bool(o.check_finite),
                         max_receivers=o.max_receivers, device=self.device, vacuum_top=o.vacuum_top,
                         vacuum_map=self.vacuum_map, grid=self.shape, layout=self.layout())
-        k = self.kernel()
-        sim.set_kernel(k["variant"], k["tile_y"], k["zchunk"], k["tile_x"])
+        _abi.fd3d_copy_kernel(sim._ctx, self._ctx)
         return sim
 
     def autotune_gradient(self, shot: dict, steps: int = 40, ckpt_every: int = 20, candidates=None) -> dict:
@@ -344,8 +343,6 @@ class Simulator:
                                        sponge=sp, sponge_alpha=o.sponge_alpha, free_surface=bool(o.free_surface),
                                        max_receivers=o.max_receivers, device=self.device, layout=self.layout())
         d = self._born_sim
-        k = self.kernel()
-        d.set_kernel(k["variant"], k["tile_y"], k["zchunk"], k["tile_x"])
         dm = [torch.as_tensor(a).to(device=self.device, dtype=self.dtype).contiguous() for a in (dlam, dmu, drho)]
         for a in dm:
             if a.shape != self.lam.shape:
@@ -355,6 +352,7 @@ class Simulator:
         rp, nrec = self._rec(rec_pos)
         traces = torch.empty((nrec, 3, self.nt), dtype=self.dtype, device=self.device)
         dtraces = torch.empty_like(traces)
+        _abi.fd3d_copy_kernel(d._ctx, self._ctx)
         _abi.fd3d_born(self._ctx, d._ctx, src, *(a.data_ptr() for a in dm), nrec, rp.ctypes.data if nrec else None,
                        traces.data_ptr() if nrec else None, dtraces.data_ptr() if nrec else None, _stream())
         self._rec_keep = (rp, w, dm)

@@ -104,3 +104,44 @@ def test_selected_kernel_runs_every_operation():
         sim.set_kernel(*kernel)
         assert [runs(sim, w) for w in ("forward", "born", "gradient")] == [want] * 3
     sim.close()
+
+
+@pytest.mark.parametrize("state", ["default", "tuned", "selected"])
+def test_copies_carry_the_choice(state):
+    """Simulator.like, and the z chunk that the batched-gradient tuner sets, leave what was
+    selected, tuned or open as it is (MIDDLE: the forward of an open choice runs rows, the other
+    operations sweeps)."""
+    from paper_2112_15071_amd.batch import BatchSimulator
+
+    sim = simulator(MIDDLE)
+    want = ["rows", "sweeps", "sweeps"]
+    if state == "tuned":
+        sim.set_tuned(dict(variant="cell", tile_x=256, tile_y=4, zchunk=32))
+    elif state == "selected":
+        sim.set_kernel("cell", 4, 32, 64)
+        want = ["rows"] * 3
+    BatchSimulator._set_zchunk([sim], 16)
+    assert sim.kernel()["zchunk"] == 16
+    copy = sim.like(NT + 1)
+    assert copy.kernel() == sim.kernel()
+    for s in (sim, copy):
+        assert [runs(s, w) for w in ("forward", "born", "gradient")] == want
+        s.close()
+
+
+def test_copy_and_depth_are_checked():
+    from paper_2112_15071_amd import _abi
+
+    a, b, c = simulator(SMALL), simulator((41, 36, 32)), simulator(SMALL, dtype=torch.float64)
+    for other in (b, c):
+        with pytest.raises(_abi.FD3DError) as e:
+            _abi.fd3d_copy_kernel(a.ctx, other.ctx)
+        assert e.value.code == _abi.FD3D_EINVAL
+    with pytest.raises(_abi.FD3DError):
+        _abi.fd3d_set_zchunk(a.ctx, 3)
+    _abi.fd3d_limit_window(a.ctx, 12 * 9 * 40 * 36 * 4)  # sweeps of 4 planes
+    _abi.fd3d_set_zchunk(a.ctx, 4)
+    with pytest.raises(_abi.FD3DError):
+        _abi.fd3d_set_zchunk(a.ctx, 5)
+    for s in (a, b, c):
+        s.close()
