@@ -249,8 +249,8 @@ int fd3d_gradient(fd3d_ctx *ctx, const fd3d_source *src, int nrec, const double 
  * With the tile kernels one velocity sweep and one stress sweep step both states.
  * ctx runs the background (src, traces: device T[nrec][3][nt] or NULL); dctx is a second
  * context over the same model arrays, grid, dtype, nt, dt, spacing, damping, field layout
- * and kernel configuration (fd3d_set_kernel), whose state holds the perturbation
- * (dtraces: device T[nrec][3][nt]).  Both states start at zero and are overwritten.
+ * and kernel configuration (fd3d_set_kernel; a context with nothing selected takes the
+ * other's), whose state holds the perturbation (dtraces: device T[nrec][3][nt]).  Both states start at zero and are overwritten.
  * Damped boundaries only; tile or cell kernels (not fused).  FD3D_EINVAL when the
  * contexts do not match. */
 int fd3d_born(fd3d_ctx *ctx, fd3d_ctx *dctx, const fd3d_source *src, const void *dlam,

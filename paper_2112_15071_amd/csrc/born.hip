@@ -9,9 +9,10 @@ using namespace fd3d;
 namespace {
 
 // Tangent-linear (Born) forward: the background steps on c and, interleaved, the
-// perturbation's steps on dc (same grid and model) fed by the Born source kernels.
+// perturbation's steps on dc (same grid and model) fed by the Born source kernels; cfg: the
+// one of them whose kernel configuration both take.
 template <typename T>
-int born_impl(fd3d_ctx *c, fd3d_ctx *dc, const fd3d_source *src, const void *dlam, const void *dmu,
+int born_impl(fd3d_ctx *c, fd3d_ctx *dc, const fd3d_ctx *cfg, const fd3d_source *src, const void *dlam, const void *dmu,
               const void *drho, int nrec, const double *rec_pos, void *traces, void *dtraces, hipStream_t st)
 {
     Inject<T> inj, dinj;
@@ -50,8 +51,8 @@ int born_impl(fd3d_ctx *c, fd3d_ctx *dc, const fd3d_source *src, const void *dla
         if (vel) born_vel_source<T><<<grd, blk, 0, st>>>(G, dv, (const T *)drho, inj, n);
         else born_stress_source<T><<<grd, blk, 0, st>>>(G, ds, (const T *)dlam, (const T *)dmu);
     };
-    const Kern kern = kernels_of(c, kBornArrays);
-    const TileMap tm = tile_map(c);
+    const Kern kern = kernels_of(cfg, kBornArrays);
+    const TileMap tm = tile_map(cfg);
     const int nwg = tm.ntx * tm.nty * tm.nzc;
     const RecJob<T> recd = rec_job<T>(D.f[VX], D.f[VY], D.f[VZ], dtaps, nrec, c->nt, (T *)dtraces);
     const RecJob<T> recg = rec_job<T>(G.f[VX], G.f[VY], G.f[VZ], taps, traces ? nrec : 0, c->nt, (T *)traces);
@@ -87,7 +88,7 @@ int born_impl(fd3d_ctx *c, fd3d_ctx *dc, const fd3d_source *src, const void *dla
                     if (!carried && r.nq > 0) record<T><<<rec_blocks(r, 256), 256, 0, st>>>(r, n);
                 continue;
             }
-            with_tile<T>(c->tile_x, c->tile_y, [&](auto tx, auto ty) {
+            with_tile<T>(cfg->tile_x, cfg->tile_y, [&](auto tx, auto ty) {
                 constexpr int TX = decltype(tx)::value, TY = decltype(ty)::value, NT = TX * TY;
                 const int nb = nwg + (recg.nq + recd.nq + NT - 1) / NT;
                 if (ntp) {
@@ -145,13 +146,17 @@ int fd3d_born(fd3d_ctx *ctx, fd3d_ctx *dctx, const fd3d_source *src, const void 
         return fail(FD3D_EINVAL, "the Born forward needs the medium at the simulation nodes");
     if (ctx->variant == FD3D_KERNEL_FUSED || dctx->variant == FD3D_KERNEL_FUSED)
         return fail(FD3D_EINVAL, "the Born forward runs the tile or cell kernels (set one with fd3d_set_kernel)");
-    if (ctx->variant != dctx->variant ||
-        (ctx->variant == FD3D_KERNEL_TILE && (ctx->tile_x != dctx->tile_x || ctx->tile_y != dctx->tile_y ||
-                                              ctx->zchunk != dctx->zchunk)))
+    // one configuration for both; a context with nothing selected takes the other's
+    const bool differ = ctx->variant != dctx->variant ||
+                        (ctx->variant == FD3D_KERNEL_TILE && (ctx->tile_x != dctx->tile_x || ctx->tile_y != dctx->tile_y ||
+                                                              ctx->zchunk != dctx->zchunk));
+    if (differ && !ctx->auto_kernel && !dctx->auto_kernel)
         return fail(FD3D_EINVAL, "the Born forward steps both contexts with one kernel configuration");
+    const fd3d_ctx *cfg = differ && ctx->auto_kernel ? dctx : ctx;
     hipStream_t st = (hipStream_t)hip_stream;
-    return ctx->tsize == 8 ? born_impl<double>(ctx, dctx, src, dlam, dmu, drho, nrec, rec_pos, traces, dtraces, st)
-                           : born_impl<float>(ctx, dctx, src, dlam, dmu, drho, nrec, rec_pos, traces, dtraces, st);
+    return ctx->tsize == 8
+               ? born_impl<double>(ctx, dctx, cfg, src, dlam, dmu, drho, nrec, rec_pos, traces, dtraces, st)
+               : born_impl<float>(ctx, dctx, cfg, src, dlam, dmu, drho, nrec, rec_pos, traces, dtraces, st);
 }
 
 } // extern "C"

@@ -145,3 +145,35 @@ def test_copy_and_depth_are_checked():
         _abi.fd3d_set_zchunk(a.ctx, 5)
     for s in (a, b, c):
         s.close()
+
+
+@pytest.mark.parametrize("selected", ["background", "perturbation"])
+def test_born_with_one_selected_context(selected):
+    """A kernel selected on one of Born's two contexts runs both when the other has nothing
+    selected (SMALL: an open choice is rows), with the bits of the open choice."""
+    from paper_2112_15071_amd import _abi
+    from paper_2112_15071_amd.simulator import make_source
+
+    ref = simulator(SMALL)
+    born(ref)()
+    want = [ref.state(), ref._born_sim.state()]  # three steps reach few receivers: the whole states
+    assert runs(ref, "born") == "rows" and all(float(x.abs().max()) > 0 for x in want)
+    from paper_2112_15071_amd import Simulator
+
+    a = simulator(SMALL)
+    b = Simulator(a.lam, a.mu, a.rho, H, DT, NT, sponge=3, layout=a.layout())
+    (a if selected == "background" else b).set_kernel("tile", 8, 32, 64)
+    sh = shot(SMALL)
+    rec = np.array(sh["rec_pos"], dtype=np.float64)
+    w = torch.ones(NT, device="cuda")
+    out = [torch.zeros((2, 3, NT), device="cuda") for _ in range(2)]
+    src = make_source(sh["src_pos"], sh["moment"], (0.0,) * 3, w)
+
+    def call():
+        _abi.fd3d_born(a.ctx, b.ctx, src, a.lam.data_ptr(), a.lam.data_ptr(), a.rho.data_ptr(), 2, rec.ctypes.data,
+                       out[0].data_ptr(), out[1].data_ptr(), torch.cuda.current_stream().cuda_stream)
+
+    assert SWEEPS["born"] <= launched(call)
+    assert torch.equal(a.state(), want[0]) and torch.equal(b.state(), want[1])
+    for s in (ref, a, b):
+        s.close()
