@@ -348,7 +348,7 @@ void fd3d_batch_destroy(fd3d_batch *b);
  * compute the same update with the same operation order per sample. */
 typedef struct fd3d_kernel {
     int variant;  /* FD3D_KERNEL_CELL, FD3D_KERNEL_TILE or FD3D_KERNEL_FUSED */
-    int tile_x;   /* tile columns: 64, 128 or 256 */
+    int tile_x;   /* tile columns: 64, 128 or 256 (the cell variant reads no tile and keeps one) */
     int tile_y;   /* tile rows: FP32 64x{4,8,16}, 128x{4,8}, 256x4; FP64 64x{4,8}, 128x4;
                      fused: FP32 64x{4,8}, FP64 64x4 */
     int zchunk;   /* z planes swept by one workgroup, >= 4 */

@@ -278,7 +278,7 @@ int fd3d_set_kernel(fd3d_ctx *ctx, const fd3d_kernel *k)
         return fail(FD3D_EINVAL, "zchunk too large: a sweep's window (zchunk + 8 planes, at most nz) must fit in 1 GiB");
     ctx->variant = k->variant;
     ctx->auto_kernel = ctx->tuned = false;
-    if (k->variant != FD3D_KERNEL_CELL) {
+    if (k->variant != FD3D_KERNEL_CELL || tile_supported(ctx->tsize, k->tile_x, k->tile_y)) {
         ctx->tile_x = k->tile_x;
         ctx->tile_y = k->tile_y;
     }
@@ -290,14 +290,9 @@ int fd3d_set_tuned(fd3d_ctx *ctx, const fd3d_kernel *k)
 {
     const int rc = fd3d_set_kernel(ctx, k);
     if (rc) return rc;
-    if (k->variant == FD3D_KERNEL_CELL) {  // the sweeps' tile beside it
-        if (tile_supported(ctx->tsize, k->tile_x, k->tile_y) && window_ok(ctx, k->zchunk)) {
-            ctx->tile_x = k->tile_x;
-            ctx->tile_y = k->tile_y;
-        } else {
-            default_tiles(ctx);
-        }
-    }
+    // the sweeps' tile beside the cell variant, or without a valid one the default
+    if (k->variant == FD3D_KERNEL_CELL && (!tile_supported(ctx->tsize, k->tile_x, k->tile_y) || !window_ok(ctx, k->zchunk)))
+        default_tiles(ctx);
     ctx->tuned = window_ok(ctx, ctx->zchunk);
     return FD3D_OK;
 }

@@ -258,8 +258,9 @@ class Simulator:
                 pass
         return dict(e, cached=False)
 
-    # kernel configurations the gradient tuner tries (variant, tile_x, tile_y, zchunk)
-    GRADIENT_CANDIDATES = (("tile", 256, 4, 64), ("tile", 256, 4, 128), ("tile", 256, 4, 0), ("tile", 128, 4, 64),
+    # kernel configurations the gradient tuner tries (variant, tile_x, tile_y, zchunk), besides
+    # this grid's own sweep; the cell variant has no tile (the values are only kept)
+    GRADIENT_CANDIDATES = (("cell", 64, 8, 32), ("tile", 256, 4, 64), ("tile", 256, 4, 128), ("tile", 256, 4, 0), ("tile", 128, 4, 64),
                            ("tile", 128, 4, 128), ("tile", 128, 8, 64), ("tile", 64, 16, 64), ("tile", 64, 8, 32))
 
     def like(self, nt: int) -> "Simulator":
@@ -279,11 +280,16 @@ class Simulator:
         ``steps`` steps (checkpoints every ``ckpt_every``, zero observed data, ``shot``'s
         source and receivers with its wavelet cut to ``steps``) on a scratch context over the
         same model for every candidate (variant, tile_x, tile_y, zchunk; zchunk 0: the whole
-        depth), and sets the fastest here.  The forward tuner (``autotune``) times the forward passes only; the adjoint
+        depth; without candidates of the caller's, this context's own sweep is one), and sets the
+        fastest here.  The forward tuner (``autotune``) times the forward passes only; the adjoint
         passes move more fields per cell and can rank tile shapes differently."""
         import time
 
-        cands = candidates or self.GRADIENT_CANDIDATES
+        cands = candidates
+        if not cands:
+            k = self.kernel()
+            own = ("tile", k["tile_x"], k["tile_y"], k["zchunk"])
+            cands = self.GRADIENT_CANDIDATES + (() if own in self.GRADIENT_CANDIDATES else (own,))
         steps = min(int(steps), self.nt)
         scratch = self.like(steps)
         gws = scratch.grad_workspace(min(ckpt_every, steps))

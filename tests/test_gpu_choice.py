@@ -177,3 +177,21 @@ def test_born_with_one_selected_context(selected):
     assert torch.equal(a.state(), want[0]) and torch.equal(b.state(), want[1])
     for s in (ref, a, b):
         s.close()
+
+
+def test_gradient_tuner_tries_the_rows_and_the_own_sweep():
+    """The tuner's candidates hold the row kernels and the sweep that the grid would run untuned
+    (60 x 50 x 45: no fixed candidate's), so that the fastest found is no slower than either."""
+    shape = (60, 50, 45)
+    sim = simulator(shape, nt=40)
+    k = sim.kernel()
+    own = f"tile,{k['tile_x']},{k['tile_y']},{k['zchunk']}"
+    assert tuple(own.split(",")) not in [tuple(map(str, c)) for c in sim.GRADIENT_CANDIDATES]
+    t = sim.autotune_gradient(shot(shape, 40))
+    assert "cell,64,8,32" in t["tried"] and own in t["tried"]
+    k = sim.kernel()
+    assert f"{k['variant']},{k['tile_x']},{k['tile_y']}," in min(t["tried"], key=t["tried"].get) + ","
+    assert runs(sim, "gradient") == {"cell": "rows", "tile": "sweeps"}[k["variant"]]
+    t = sim.autotune_gradient(shot(shape, 40), candidates=[("tile", 64, 8, 32)])  # the caller's only
+    assert list(t["tried"]) == ["tile,64,8,32"] and sim.kernel()["variant"] == "tile"
+    sim.close()
