@@ -320,6 +320,13 @@ int fd3d_batch_set_schedule(fd3d_batch *b, size_t group_bytes);
  * Synchronises the stream. */
 int fd3d_batch_autotune(fd3d_batch *b, int steps, int best[6], double *best_ms, void *hip_stream);
 
+/* Sweeps of the batched gradient alone: tile shape and depth (0: each shot's whole depth) for
+ * every shot, whatever is selected on the batch or its contexts; tile_x = tile_y = 0: what the
+ * library picks when nothing is selected on the batch (cell kernels while all shots' arrays stay
+ * in the cache, else a shape and depth that fit the shots).  Without this call, and after a later
+ * fd3d_batch_set_tiles or _set_kernel, the gradient follows the batch's tile shapes. */
+int fd3d_batch_set_gradient(fd3d_batch *b, int tile_x, int tile_y, int zchunk);
+
 /* srcs[nshot] (or NULL), nrec[nshot], rec_pos[nshot] (host double[nrec][3] each),
  * traces[nshot] (device T[nrec][3][nt] each); flags as fd3d_forward. */
 int fd3d_batch_forward(fd3d_batch *b, const fd3d_source *srcs, const int *nrec,

@@ -109,6 +109,7 @@ _SIGS = {
     "fd3d_get_adjoint_state": ([_vp, _vp, ctypes.POINTER(_vp), _vp], _i),
     "fd3d_batch_workspace_bytes": ([_i, ctypes.POINTER(_vp), ctypes.POINTER(_sz)], _i),
     "fd3d_batch_create": ([ctypes.POINTER(_vp), _i, ctypes.POINTER(_vp), _vp, _sz], _i),
+    "fd3d_batch_set_gradient": ([_vp, _i, _i, _i], _i),
     "fd3d_batch_set_kernel": ([_vp, _i, _i, _i], _i),
     "fd3d_batch_set_tiles": ([_vp, _i, _i, _i, _i, _i], _i),
     "fd3d_batch_set_schedule": ([_vp, _sz], _i),
@@ -262,6 +263,10 @@ def fd3d_batch_set_kernel(batch, tile_x: int, tile_y: int, workgroups: int = 0) 
 def fd3d_batch_set_tiles(batch, tile_x: int, tile_y: int, tile2_x: int = 0, tile2_y: int = 0,
                          workgroups: int = 0) -> None:
     _check(_lib.fd3d_batch_set_tiles(batch, int(tile_x), int(tile_y), int(tile2_x), int(tile2_y), int(workgroups)))
+
+
+def fd3d_batch_set_gradient(batch, tile_x: int, tile_y: int, zchunk: int = 0) -> None:
+    _check(_lib.fd3d_batch_set_gradient(batch, int(tile_x), int(tile_y), int(zchunk)))
 
 
 def fd3d_batch_set_schedule(batch, group_bytes: int) -> None:

@@ -37,6 +37,12 @@ class BatchSimulator:
         t2 = tile2 or (0, 0)
         _abi.fd3d_batch_set_tiles(self._b, tile_x, tile_y, t2[0], t2[1], workgroups)
 
+    def set_gradient_kernel(self, tile_x: int = 0, tile_y: int = 0, zchunk: int = 0) -> None:
+        """Sweeps of the batched gradient alone: tile shape and depth (0: each shot's whole
+        depth); without a shape, the library's choice (row kernels, or sweeps that fit the
+        shots).  A later ``set_kernel`` applies to the gradient again."""
+        _abi.fd3d_batch_set_gradient(self._b, tile_x, tile_y, zchunk)
+
     def set_schedule(self, group_bytes: int = 0) -> None:
         """Order of the batched forward: 0 = lockstep (every launch covers every shot);
         otherwise cache-blocked groups of shots whose fields and models add up to at most
@@ -63,8 +69,9 @@ class BatchSimulator:
 
     # (tile_x, tile_y, zchunk) configurations the batched-gradient tuner tries; zchunk 0:
     # each shot's whole depth (with several shots per launch, whole-depth sweeps can fill
-    # the chip where one shot's cannot)
-    GRADIENT_CANDIDATES = ((256, 4, 64), (256, 4, 128), (256, 4, 0), (128, 8, 64), (128, 4, 64), (128, 4, 128),
+    # the chip where one shot's cannot); tile 0 x 0: the library's choice, whose sweeps are
+    # at least 4 planes deep and which leaves the simulators' z chunks as they are
+    GRADIENT_CANDIDATES = ((0, 0, 4), (256, 4, 64), (256, 4, 128), (256, 4, 0), (128, 8, 64), (128, 4, 64), (128, 4, 128),
                            (64, 16, 64), (64, 8, 32))
 
     @staticmethod
@@ -73,11 +80,12 @@ class BatchSimulator:
             _abi.fd3d_set_zchunk(sim.ctx, zc if zc > 0 else sim.shape[2])
 
     def autotune_gradient(self, shots: List[Dict], steps: int = 40, ckpt_every: int = 20, candidates=None) -> dict:
-        """Pick the tile shape and z chunk of the batched gradient: times the batched
-        gradient over ``steps`` steps (checkpoints every ``ckpt_every``, zero observed data,
-        each shot's wavelet cut to ``steps``) on scratch contexts over the same models for
-        every candidate (tile_x, tile_y, zchunk), then sets the fastest tile shape here and
-        its z chunk on every simulator of the batch."""
+        """Pick the kernels of the batched gradient: times the batched gradient over ``steps``
+        steps (checkpoints every ``ckpt_every``, zero observed data, each shot's wavelet cut
+        to ``steps``) on scratch contexts over the same models for every candidate (tile_x,
+        tile_y, zchunk), then sets the fastest for the gradient here (``set_gradient_kernel``;
+        the forward keeps its kernels and schedule) and its z chunk on every simulator of the
+        batch."""
         import time
 
         from .simulator import _shot_args
@@ -95,8 +103,7 @@ class BatchSimulator:
         for c in candidates or self.GRADIENT_CANDIDATES:
             tx, ty, zc = c
             try:
-                sb.set_kernel(tx, ty)
-                BatchSimulator._set_zchunk(scratch, zc)
+                sb.set_gradient_kernel(tx, ty, zc)
             except _abi.FD3DError:
                 continue  # a shape not built for this dtype, or too deep a window
             sb.gradient(args, d_obs, *g, ckpt_every=ck, gws=gws)
@@ -111,8 +118,9 @@ class BatchSimulator:
         if not times:
             raise RuntimeError("no batched-gradient configuration runs for this batch")
         best = min(times, key=times.get)
-        self.set_kernel(best[0], best[1])
-        BatchSimulator._set_zchunk(self.sims, best[2])
+        self.set_gradient_kernel(*best)
+        if best[0] > 0:
+            BatchSimulator._set_zchunk(self.sims, best[2])
         return dict(tile=[best[0], best[1]], zchunk=self.sims[0].kernel()["zchunk"], ms_per_step=times[best],
                     tried={f"{x}x{y},{z if z else 'nz'}": round(v, 4) for (x, y, z), v in times.items()})
 

@@ -362,9 +362,8 @@ int batch_gradient_impl(fd3d_batch *b, const fd3d_source *srcs, const int *nrec,
     std::vector<AdjGrid<T>> ag(S);
     int tiles = 0, rtiles = 0, recs = 0, ncol = 0;
     int cbase[kMaxBatchColors] = {0, 0, 0, 0};
-    BatchGroup all = whole_batch(b);  // every shot in each launch (lockstep)
-    const bool row_adj = batch_rows(b->tiles_set, b->ctx.data(), S, kAdjointArrays);
-    if (!row_adj) fit_sweeps(all, S, b->tiles_set, [&](int q) { return b->ctx[q]; });
+    BatchGroup all;  // every shot in each launch (lockstep)
+    const bool row_fwd = gradient_group(b, all);
     for (int s = 0; s < S; ++s) {
         fd3d_ctx *c = b->ctx[s];
         const std::string tag = "shot " + std::to_string(s) + ": ";
@@ -482,8 +481,7 @@ int batch_gradient_impl(fd3d_batch *b, const fd3d_source *srcs, const int *nrec,
     all.rtiles = rtiles;
     all.recs = recs;
     BatchGroup fwd = all;
-    if (batch_rows(b->tiles_set, b->ctx.data(), S, kForwardArrays)) fwd.rows = batch_row_maps(b);
-    if (row_adj) all.rows = batch_row_maps(b);
+    if (row_fwd) fwd.rows = batch_row_maps(b);
 
     const bool merged = all.rows || all.tx2 == 0;  // stress-M (row kernels, or one tile shape)
     // forward with checkpoints
@@ -609,6 +607,7 @@ int fd3d_batch_create(fd3d_batch **out, int nshot, fd3d_ctx *const *ctxs, void *
     else { b->tile_x = 64; b->tile_y = 8; }
     b->wgs_req = 0;
     b->tiles_set = b->sched_set = false;
+    b->grad_x = -1;
     b->tile2_x = b->tile2_y = 0;
     b->staged_pending = false;
     b->graph_valid = false;
@@ -646,6 +645,23 @@ int fd3d_batch_set_tiles(fd3d_batch *b, int tile_x, int tile_y, int tile2_x, int
     b->tile2_y = tile2_y;
     b->wgs_req = workgroups;
     b->tiles_set = true;
+    b->grad_x = -1;
+    return FD3D_OK;
+}
+
+int fd3d_batch_set_gradient(fd3d_batch *b, int tile_x, int tile_y, int zchunk)
+{
+    if (!b) return fail(FD3D_EINVAL, "batch is NULL");
+    const bool own = tile_x == 0 && tile_y == 0;  // the library's choice
+    if (!own && !tile_supported(b->tsize, tile_x, tile_y))
+        return fail(FD3D_EINVAL, "unsupported tile shape " + std::to_string(tile_x) + "x" + std::to_string(tile_y));
+    if (!own && zchunk != 0 && zchunk < 4) return fail(FD3D_EINVAL, "zchunk must be 0 (the whole depth) or >= 4");
+    for (const fd3d_ctx *c : b->ctx)
+        if (!own && !window_ok(c, zchunk > 0 ? zchunk : c->n[2]))
+            return fail(FD3D_EINVAL, "zchunk too large for a tile sweep");
+    b->grad_x = tile_x;
+    b->grad_y = tile_y;
+    b->grad_z = zchunk;
     return FD3D_OK;
 }
 

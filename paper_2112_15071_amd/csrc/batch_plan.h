@@ -22,6 +22,7 @@ struct BatchGroup {
     int tx, ty, tx2, ty2;
     int vac;  // some shot of the group has a vacuum surface
     int zc;   // depth of the launch for shots with nothing selected (0: each shot's own)
+    int every_zc;  // depth of every shot, selected or not (0: the above)
     int rtiles;              // row kernels: their blocks
     const ShotRows *rows;    // and the shots' shares of them (null: tile kernels)
     int ntp;  // cache policy of the group's forward passes (see group_streams)
@@ -41,6 +42,8 @@ struct fd3d_batch {
     bool tiles_set;        // the caller or the tuner selected the batch's tile shapes
     size_t group_bytes;    // 0: lockstep; otherwise the cache-blocked group budget
     bool sched_set;        // the caller or the tuner selected the schedule
+    int grad_x, grad_y, grad_z;  // tile shape and depth of the gradient's sweeps (x < 0: as the
+                                 // batch's tiles are set; 0: the library's choice; z 0: whole depth)
     std::vector<fd3d::BatchGroup> groups;
     std::vector<int> order;  // shot at each position of the descriptor arrays
     std::vector<unsigned char> fwd_host, rec_host;
@@ -111,7 +114,8 @@ inline TileMap shot_tiles(const BatchGroup &b, const fd3d_ctx *c, int &alt)
     TileMap tm;
     tm.ntx = (c->n[0] + tx - 1) / tx;
     tm.nty = (c->n[1] + ty - 1) / ty;
-    tm.zc = c->auto_kernel && b.zc > 0 ? sweep_depth(c, b.zc) : c->zchunk;
+    tm.zc = b.every_zc > 0 ? std::min(b.every_zc, std::max(4, c->n[2]))
+            : c->auto_kernel && b.zc > 0 ? sweep_depth(c, b.zc) : c->zchunk;
     tm.nzc = (c->n[2] + tm.zc - 1) / tm.zc;
     return tm;
 }
@@ -162,6 +166,26 @@ inline bool batch_rows(bool tiles_set, const fd3d_ctx *const *ctx, int ns, int a
 
 // Where the batch workspace holds the shots' row maps.
 inline const ShotRows *batch_row_maps(const fd3d_batch *b) { return (const ShotRows *)(b->ws + b->off_rows); }
+
+// Kernels of the batched gradient, which steps every shot in each launch: the group of its adjoint
+// passes and recompute (gr.rows: row kernels), and whether its forward runs rows.
+inline bool gradient_group(const fd3d_batch *b, BatchGroup &gr)
+{
+    const bool tiles = b->grad_x != 0 && (b->grad_x > 0 || b->tiles_set);
+    auto shot = [&](int q) { return b->ctx[q]; };
+    gr = whole_batch(b);
+    if (b->grad_x > 0) {
+        gr.tx = b->grad_x;
+        gr.ty = b->grad_y;
+        gr.tx2 = gr.ty2 = 0;
+        gr.every_zc = b->grad_z > 0 ? b->grad_z : 1 << 30;
+    } else if (batch_rows(tiles, b->ctx.data(), b->nshot, kAdjointArrays)) {
+        gr.rows = batch_row_maps(b);
+    } else {
+        fit_sweeps(gr, b->nshot, tiles, shot);
+    }
+    return batch_rows(tiles, b->ctx.data(), b->nshot, kForwardArrays);
+}
 
 // Working set of one shot in the step loop: nine fields and the three model arrays.
 inline size_t shot_footprint(const fd3d_ctx *c) { return (size_t)12 * c->n[0] * c->n[1] * c->n[2] * c->tsize; }

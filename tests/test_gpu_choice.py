@@ -195,3 +195,69 @@ def test_gradient_tuner_tries_the_rows_and_the_own_sweep():
     t = sim.autotune_gradient(shot(shape, 40), candidates=[("tile", 64, 8, 32)])  # the caller's only
     assert list(t["tried"]) == ["tile,64,8,32"] and sim.kernel()["variant"] == "tile"
     sim.close()
+
+
+def batch_of(n=2):
+    from paper_2112_15071_amd.batch import BatchSimulator
+
+    sims = [simulator(SMALL, nt=6) for _ in range(n)]
+    return BatchSimulator(sims), sims, [shot(SMALL, 6)] * n
+
+
+def batch_runs(batch, sims, shots, what) -> str:
+    obs = [torch.zeros((2, 3, s.nt), device="cuda") for s in sims]
+    g = [[torch.zeros_like(s.lam) for s in sims] for _ in range(3)]
+    call = {"forward": lambda: batch.forward(shots, use_graph=False),
+            "gradient": lambda: batch.gradient(shots, obs, *g, ckpt_every=3)}[what]
+    names = launched(call)
+    kinds = {k for k in ("row", "tile") if {f"vel_{k}_multi", f"stress_{k}_multi"} & names}
+    assert len(kinds) == 1, names
+    return {"row": "rows", "tile": "sweeps"}[kinds.pop()]
+
+
+def test_batched_gradient_tuner_leaves_the_forward_alone():
+    """Two small shots: forward and gradient run rows by default.  The gradient tuner tries that
+    too, and what it sets counts for the gradient alone, until tiles are selected on the batch."""
+    batch, sims, shots = batch_of()
+    both = lambda: [batch_runs(batch, sims, shots, w) for w in ("forward", "gradient")]
+    assert both() == ["rows", "rows"]
+    zc = sims[0].kernel()["zchunk"]
+    t = batch.autotune_gradient(shots, steps=6, ckpt_every=3)
+    assert "0x0,4" in t["tried"] and len(t["tried"]) > 5
+    assert both() == ["rows", "rows" if t["tile"] == [0, 0] else "sweeps"]
+    assert t["zchunk"] == sims[0].kernel()["zchunk"] and (t["tile"] != [0, 0] or t["zchunk"] == zc)
+    t = batch.autotune_gradient(shots, steps=6, ckpt_every=3, candidates=[(64, 8, 16)])
+    assert t["tile"] == [64, 8] and t["zchunk"] == 16 == sims[1].kernel()["zchunk"]
+    assert both() == ["rows", "sweeps"]
+    t = batch.autotune_gradient(shots, steps=6, ckpt_every=3, candidates=[(0, 0, 4)])
+    assert both() == ["rows", "rows"]
+    batch.set_kernel(64, 8)
+    assert both() == ["sweeps", "sweeps"]
+    batch.close()
+    for s in sims:
+        s.close()
+
+
+def test_batched_gradient_kernels_give_the_same_bits():
+    """Every shape and depth (whole, ragged, deeper than the grid) of the gradient's sweeps, and
+    the library's choice; unsupported shapes and depths are refused."""
+    from paper_2112_15071_amd import _abi
+
+    batch, sims, shots = batch_of()
+    rng = np.random.default_rng(2)
+    obs = [torch.as_tensor(rng.standard_normal((2, 3, 6)) * 1e-6, dtype=torch.float32, device="cuda") for _ in sims]
+    ref = None
+    for k in [(0, 0, 0), (64, 8, 0), (64, 16, 5), (128, 4, 64), (256, 4, 32)]:
+        batch.set_gradient_kernel(*k)
+        g = [[torch.zeros_like(s.lam) for s in sims] for _ in range(3)]
+        tr, J = batch.gradient(shots, obs, *g, ckpt_every=4)
+        out = [*tr, J, *(x for q in g for x in q)]
+        ref = ref or out
+        assert all(torch.equal(a, b) for a, b in zip(ref, out)), k
+    assert all(float(x.abs().max()) > 0 for x in ref[-6:])
+    for bad in [(64, 5, 8), (0, 8, 8), (64, 8, 3), (-1, -1, 0)]:
+        with pytest.raises(_abi.FD3DError):
+            batch.set_gradient_kernel(*bad)
+    batch.close()
+    for s in sims:
+        s.close()
