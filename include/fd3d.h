@@ -131,7 +131,8 @@ typedef struct fd3d_source {
 
 typedef struct fd3d_ctx fd3d_ctx;
 
-/* Library version string (static storage). */
+/* Library version string (static storage); it changes with the kernels that tuned results
+ * refer to. */
 const char *fd3d_version(void);
 
 /* Message of the last failed call on this thread ("" if none). */

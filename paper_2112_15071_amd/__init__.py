@@ -5,7 +5,7 @@ torch supplying device memory and streams.
 The HIP library is required: importing ``Simulator`` loads ``libfd3d.so`` and fails
 loudly if it is missing.  There is no CPU fallback.
 """
-__version__ = "0.1.0"
+__version__ = "0.2.0"
 
 
 def __getattr__(name):

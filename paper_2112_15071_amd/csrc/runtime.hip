@@ -389,7 +389,7 @@ void zero_fields_any(fd3d_ctx *c, hipStream_t st)
 
 extern "C" {
 
-const char *fd3d_version(void) { return "fd3d 0.1.0 (gfx950)"; }
+const char *fd3d_version(void) { return "fd3d 0.2.0 (gfx950)"; }
 
 const char *fd3d_last_error(void) { return g_err.c_str(); }
 

@@ -225,13 +225,13 @@ class Simulator:
     def autotune(self, steps: int = 20, cache: bool = True) -> dict:
         """Pick the fastest kernel variant, tile shape and z chunk of the forward for this grid
         (fd3d_autotune; Born and the gradient keep the library's choice between rows and sweeps),
-        with a JSON cache keyed by grid shape, dtype, free surface and device (CU count, memory size)
-        ($FD3D_AUTOTUNE_CACHE, default ~/.cache/fd3d/autotune.json).  Zeroes the state."""
+        with a JSON cache keyed by grid shape, dtype, free surface, device (CU count, memory size)
+        and library version, whose kernels it timed ($FD3D_AUTOTUNE_CACHE, default ~/.cache/fd3d/autotune.json).  Zeroes the state."""
         nx, ny, nz = self.shape
         props = torch.cuda.get_device_properties(self.device)
         dev = f"{props.multi_processor_count}cu-{props.total_memory >> 30}gib"
         cm = "" if self.coarse is None else "/cm{}x{}x{}".format(*self.coarse)
-        key = f"{nx}x{ny}x{nz}/{str(self.dtype)}/fs{int(self.opts.free_surface)}{cm}/{self.layout()}/{dev}"
+        key = f"{nx}x{ny}x{nz}/{str(self.dtype)}/fs{int(self.opts.free_surface)}{cm}/{self.layout()}/{dev}/{_abi.fd3d_version()}"
         path = os.environ.get("FD3D_AUTOTUNE_CACHE", os.path.expanduser("~/.cache/fd3d/autotune.json"))
         table = {}
         if cache and os.path.exists(path):

@@ -261,3 +261,21 @@ def test_batched_gradient_kernels_give_the_same_bits():
     batch.close()
     for s in sims:
         s.close()
+
+
+def test_saved_tuning_of_another_version_is_not_taken(tmp_path, monkeypatch):
+    """A saved result counts for the library version that timed it: a table without the version
+    in its keys, or of another one, is tuned anew and kept beside."""
+    from paper_2112_15071_amd import _abi
+
+    path = tmp_path / "tuned.json"
+    monkeypatch.setenv("FD3D_AUTOTUNE_CACHE", str(path))
+    sim = simulator(SMALL)
+    assert not sim.autotune(steps=1)["cached"] and sim.autotune(steps=1)["cached"]
+    (key, e), = json.loads(path.read_text()).items()
+    assert key.endswith(_abi.fd3d_version())
+    for old in (key[:-len(_abi.fd3d_version()) - 1], key + ".older"):
+        path.write_text(json.dumps({old: e}))
+        assert not sim.autotune(steps=1)["cached"]
+        assert set(json.loads(path.read_text())) == {old, key}
+    sim.close()
