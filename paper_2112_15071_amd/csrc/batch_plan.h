@@ -146,22 +146,22 @@ template <typename C> void fit_sweeps(BatchGroup &g, int ns, bool tiles_set, C &
 }
 
 // Whether a launch over these shots runs the row kernels: when neither the batch has tile shapes
-// selected nor a shot a tile or fused kernel, and the arrays of all shots (`arrays` each) together
-// stay in the Infinity Cache (kernels_of).  In lockstep, us per step, rows / best tile sweep (with the depth
+// selected nor a shot a tile or fused kernel, and all shots' arrays (`arrays` each) together are of
+// a size that the row kernels are for (kernels_of).  In lockstep, us per step, rows / best tile sweep (with the depth
 // of one round), forward and gradient: six shots of 40 x 50 x 60 30.0 / 31.6 and 112.9 / 133.6,
 // eight of 64^3 46.7 / 50.6 and 208.7 / 212.1, four of 96 x 80 x 72 (106 MB) 54.1 / 54.3 and 244.2
 // / 244.3, four of 128 x 96 x 80 (189 MB) 71.5 / 79.7 and 342.3 / 348.2.
 inline bool batch_rows(bool tiles_set, const fd3d_ctx *const *ctx, int ns, int arrays)
 {
     if (tiles_set) return false;
-    double bytes = 0.0;
+    RowSize size;
     if (ns == 1 && arrays == kForwardArrays) return kernels_of(ctx[0], arrays) == Kern::rows;
     for (int q = 0; q < ns; ++q) {
         const fd3d_ctx *c = ctx[q];
         if (!rows_ok(c) || (!unselected(c, arrays) && c->variant != FD3D_KERNEL_CELL)) return false;
-        bytes += (double)arrays * c->n[0] * c->n[1] * c->n[2] * c->tsize;
+        size.add(c, arrays);
     }
-    return bytes <= (ctx[0]->tsize == 8 ? kRowBytes64 : kRowBytes32);
+    return size.pays(ctx[0]->tsize);
 }
 
 // Where the batch workspace holds the shots' row maps.

@@ -478,15 +478,39 @@ inline bool cells_ok(const fd3d_ctx *c) { return c->n[2] <= kMaxGridYZ && (c->n[
 
 // Kernels of an operation that steps `arrays` cell-sized arrays: rows, tile sweeps, or the
 // kernels with a bounds test per load (cells).  A selected variant decides, one that the tuner
-// found for the forward, which alone it timed; with nothing selected, the rows run while the arrays stay in the Infinity Cache, and else the sweeps.
-// Measured on both sides of the limit (FP32, MI355X, us per step, rows / best tile sweep): the
-// forward's 12 arrays at 192 x 192 x 128 (226 MB) 89 / 94 and 256 x 256 x 96 (302 MB) 156 / 133;
-// Born's 24 at 128^3 (201 MB) 74 / 94 and 192 x 160 x 128 (377 MB) 210 / 185; the adjoint's 29 at
-// 149 x 101 x 87 (152 MB) 159 / 183, 128^3 (243 MB) 201 / 202 and 192 x 160 x 128 (456 MB)
-// 380 / 369 (whole gradients).  FP64 rows hold twice the registers and halve the waves in
-// flight: 48^3 14.7 / 22.4, 120 x 112 x 104 (134 MB) 71 / 61.
+// found for the forward, which alone it timed; with nothing selected, the size (RowSize).
+// FP32 rows run while the arrays stay in the Infinity Cache.  Measured on both sides of the limit
+// (MI355X, us per step, rows / best tile sweep): the forward's 12 arrays at 192 x 192 x 128 (226
+// MB) 89 / 94, 72 x 256 x 220 (195 MB, few lanes filled) 105 / 101 and 256 x 256 x 96 (302 MB) 156
+// / 133; Born's 24 at 128^3 (201 MB) 74 / 94, 33 x 256 x 256 (208 MB) 112 / 120 and 192 x 160 x 128
+// (377 MB) 210 / 185; the adjoint's 29 at 149 x 101 x 87 (152 MB) 147 / 167, 128^3 (243 MB) 201 /
+// 202 and 192 x 160 x 128 (456 MB) 380 / 369 (whole gradients).
+// FP64 rows hold twice the registers, which halves the waves in flight, and from some 400 thousand
+// lanes on (idle ones past a row's end included) the sweeps are as fast in every operation, where
+// the rows fill their lanes from 660 thousand.  Forward, Born, gradient, rows / best sweep, in
+// thousands of lanes: 48 x 80 x 64 (328) 20 / 25, 37 / 41, 78 / 91; 72 x 56 x 56 (401) 25 / 25, 44 /
+// 42, 93 / 93; 90 x 60 x 60 (461) 28 / 26, 51 / 47, 107 / 101; 120 x 64 x 64 (524, 94 % filled) 30
+// / 30, 54 / 59, 121 / 119; 128 x 80 x 64 (655, all) 35 / 37, 66 / 69, 147 / 145; 88 x 88 x 80 (991)
+// 44 / 39, 82 / 73, 176 / 157; 110 x 100 x 96 (1229, 86 %) 58 / 52, 114 / 102, 275 / 224; batches'
+// forward: two of 64^3 (524, all) 33 / 33, six of 40^3 (614, 63 %) 37 / 34.
 constexpr int kForwardArrays = 12, kBornArrays = 24, kAdjointArrays = 29;
-constexpr double kRowBytes32 = 230.0 * 1024 * 1024, kRowBytes64 = 64.0 * 1024 * 1024;
+constexpr double kRowBytes32 = 230.0 * 1024 * 1024, kRowLanes64 = 400e3, kFullRowLanes64 = 660e3;
+struct RowSize {  // of the row launches of one operation over some grids
+    double bytes = 0.0, cells = 0.0, lanes = 0.0;
+
+    void add(const fd3d_ctx *c, int arrays)
+    {
+        const RowMap rm = row_map(c);
+        const double rows = (double)c->n[1] * c->n[2];
+        cells += rows * c->n[0];
+        lanes += rows * (rm.ntx << rm.lbx);
+        bytes += rows * c->n[0] * arrays * c->tsize;
+    }
+    bool pays(int tsize) const
+    {
+        return tsize == 8 ? lanes <= (cells >= 0.9 * lanes ? kFullRowLanes64 : kRowLanes64) : bytes <= kRowBytes32;
+    }
+};
 enum class Kern { rows, tiles, cells };
 inline bool unselected(const fd3d_ctx *c, int arrays) { return c->auto_kernel || (c->tuned && arrays != kForwardArrays); }
 inline Kern kernels_of(const fd3d_ctx *c, int arrays)
@@ -494,8 +518,9 @@ inline Kern kernels_of(const fd3d_ctx *c, int arrays)
     if (!unselected(c, arrays))
         return c->variant != FD3D_KERNEL_CELL ? Kern::tiles : rows_ok(c) ? Kern::rows : Kern::cells;
     if (coarse_on(c->opts)) return Kern::tiles;
-    const double bytes = (double)arrays * c->n[0] * c->n[1] * c->n[2] * c->tsize;
-    return bytes <= (c->tsize == 8 ? kRowBytes64 : kRowBytes32) && rows_ok(c) ? Kern::rows : Kern::tiles;
+    RowSize size;
+    size.add(c, arrays);
+    return size.pays(c->tsize) && rows_ok(c) ? Kern::rows : Kern::tiles;
 }
 
 // Default tile shape and sweep depth (choose_sweep).  False when no sweep fits one window.

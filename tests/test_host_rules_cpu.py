@@ -158,3 +158,15 @@ def test_groups_use_the_tuned_sweep(ask):
         assert groups(ask, (0, 0), 400, [(big, kernel), (big, kernel)]) == [(2, 0, *tile)], kernel
     assert groups(ask, (0, 0), 400, [(big, TUNED_CELL), (big, TUNED_TILE)]) == [(2, 0, 64, 16)]
     assert [g[1] for g in groups(ask, (0, 0), 160, [(big, TUNED_CELL)] * 2)] == [1, 1]
+
+
+def test_fp64_rows_by_their_lanes(ask):
+    """In FP64 every operation, and the shots of a launch together, run rows up to 400 thousand
+    lanes, or 660 thousand with nine in ten filled (measured on both sides)."""
+    cases = [((64, 64, 64), 0), ((48, 80, 64), 0), ((120, 64, 64), 0), ((128, 80, 64), 0), ((72, 56, 56), 1),
+             ((72, 64, 64), 1), ((90, 60, 60), 1), ((128, 82, 64), 1), ((120, 112, 104), 1)]
+    got = ask(["kern 8 0 0 0 0 %d %d %d -1 0 0" % g for g, _ in cases])
+    for (g, want), r in zip(cases, got):
+        assert r == [want] * 3, g
+    for shots, want in ([(64, 64, 64)] * 2, 1), ([(40, 40, 40)] * 3, 1), ([(40, 40, 40)] * 6, 0):
+        assert [g[1] for g in groups(ask, (0, 0), 0, [(s, NONE) for s in shots], ts=8)] == [want], shots
