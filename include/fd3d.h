@@ -272,7 +272,8 @@ int fd3d_get_adjoint_state(fd3d_ctx *ctx, const void *gws, void *const fields[9]
  * step runs as ONE persistent launch over the flat list of every shot's tiles (the list
  * is split into 8 contiguous chunks, one per XCD); with use_graph the whole nt-step
  * sequence is captured once into a hipGraph and replayed by one hipGraphLaunch on the
- * caller's stream (recaptured when the tiling or receiver counts change).  Per-shot
+ * caller's stream (recaptured when the tiling or receiver counts change; a sequence of more
+ * than 65536 launches, two per step and group, is launched step by step).  Per-shot
  * results are identical to fd3d_forward on each context with the same tile shape.
  * fd3d_batch_set_schedule switches the forward from this lockstep order to
  * cache-blocked groups (the gradient always runs lockstep).

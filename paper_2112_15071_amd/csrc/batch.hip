@@ -271,7 +271,7 @@ int batch_forward_impl(fd3d_batch *b, const fd3d_source *srcs, const int *nrec, 
                        (long)g.tx2, (long)g.ty2, (long)g.vac, (long)(g.rows != nullptr), (long)g.rtiles})
             mix(v);
     }
-    if (!use_graph) return batch_sequence<T>(b, flags, st);
+    if (!use_graph || !graph_fits(b)) return batch_sequence<T>(b, flags, st);
     if (!b->graph_valid || b->graph_key != (long)key) {
         if (b->graph_valid) {
             (void)hipGraphExecDestroy(b->gexec);

@@ -5,6 +5,7 @@
 // "groups <tsize> 0 <tile_x> <tile_y> <group MiB> {<nx ny nz> <kernel> 0 0}..." the groups of a batch:
 // tile_x 0: no tile shapes selected, group MiB -1: no schedule, kernel: -1 none or FD3D_KERNEL_*
 // (tiles of 64 x 16), 10 more: the tuner's; answers shots, rows, tile_x, tile_y of each group.
+// "graph <tsize> 0 <steps> 0 <group MiB> {as groups}..." whether a batch's sequence is captured.
 // "kern <tsize> <coarse> 0 0 0 <nx ny nz> <kernel> 0 0" what forward, Born and adjoint run
 // (0 rows, 1 sweeps, 2 kernels with a bounds test per load).  "tuner <tsize> 0 <nx ny nz>" runs
 // fd3d_autotune where there is no device, so that it fails, and prints its return code and
@@ -38,7 +39,7 @@ int main()
         in >> what >> ts >> cm;
         std::vector<fd3d_ctx> g;
         int tx = 0, ty = 0, mib = 0;
-        const bool select = what == "groups" || what == "kern";
+        const bool select = what == "groups" || what == "kern" || what == "graph";
         if (select) in >> tx >> ty >> mib;
         while (in >> nx >> ny >> nz) {
             g.push_back(grid(nx, ny, nz, ts, cm));
@@ -58,7 +59,10 @@ int main()
             std::printf("%d %d", s.tx, s.ty);
             for (auto &c : g) std::printf(" %d", s.zc ? fd3d::sweep_depth(&c, s.zc) : 0);
             std::printf("\n");
-        } else if (what == "groups") {
+        } else if (what == "groups" || what == "graph") {
+            const bool graph = what == "graph";
+            const int steps = tx;
+            if (graph) tx = 0;
             fd3d_batch b{};
             char ws = 0;
             b.nshot = (int)g.size();
@@ -71,6 +75,11 @@ int main()
             b.sched_set = mib >= 0;
             b.group_bytes = mib > 0 ? (size_t)mib << 20 : 0;
             fd3d::make_groups(&b);
+            if (graph) {
+                b.nt = steps;
+                std::printf("%d\n", (int)fd3d::graph_fits(&b));
+                continue;
+            }
             for (const fd3d::BatchGroup &r : b.groups) std::printf("%d %d %d %d ", r.ns, (int)(r.rows != nullptr), r.tx, r.ty);
             std::printf("\n");
         } else if (what == "kern") {

@@ -76,3 +76,27 @@ def test_full_size_lockstep(monkeypatch):
 
     monkeypatch.setattr(BatchSimulator, "__init__", lockstep)
     batches.test_full_size_uneven_batch_truncated()
+
+
+def test_long_sequence():
+    """Two shots of 20000 steps in groups of one (80000 launches, more than are captured) give the
+    lockstep batch's traces (40000 launches, a graph), asked for a graph twice each."""
+    from paper_2112_15071_amd import Simulator
+    from paper_2112_15071_amd.batch import BatchSimulator
+
+    nt = 20000
+    (model, sh) = setup((7, 6, 5))
+    sh["wavelet"] = np.exp(-((np.arange(nt) - 30.0) / 9.0) ** 2)
+    sims = [Simulator(*model, H, DT, nt, sponge=3) for _ in range(2)]
+    out = []
+    for budget in (1, 0):
+        batch = BatchSimulator(sims)
+        batch.set_schedule(budget)
+        for _ in range(2):
+            out.append([t.clone() for t in batch.forward([sh, sh], use_graph=True)])
+        batch.close()
+    for o in out[1:]:
+        assert all(torch.equal(a, b) for a, b in zip(out[0], o))
+    assert all(float(t.abs().max()) > 0 for t in out[0])
+    for s in sims:
+        s.close()

@@ -170,3 +170,12 @@ def test_fp64_rows_by_their_lanes(ask):
         assert r == [want] * 3, g
     for shots, want in ([(64, 64, 64)] * 2, 1), ([(40, 40, 40)] * 3, 1), ([(40, 40, 40)] * 6, 0):
         assert [g[1] for g in groups(ask, (0, 0), 0, [(s, NONE) for s in shots], ts=8)] == [want], shots
+
+
+def test_long_sequences_are_not_captured(ask):
+    """A batch's sequence becomes a graph up to 65536 launches, two per step and group: in
+    lockstep by the steps alone, in groups by their number too."""
+    shots = lambda n: " ".join("64 64 64 -1 0 0" for _ in range(n))
+    cases = [(32768, 0, 24, 1), (32769, 0, 1, 0), (4096, 12, 8, 1), (4097, 12, 8, 0), (8000, 12, 16, 0), (8000, -1, 16, 1)]
+    got = ask([f"graph 4 0 {nt} 0 {mib} {shots(n)}" for nt, mib, n, _ in cases])
+    assert [r[0] for r in got] == [c[3] for c in cases]
