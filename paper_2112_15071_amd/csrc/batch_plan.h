@@ -147,10 +147,11 @@ template <typename C> void fit_sweeps(BatchGroup &g, int ns, bool tiles_set, C &
 
 // Whether a launch over these shots runs the row kernels: when neither the batch has tile shapes
 // selected nor a shot a tile or fused kernel, and all shots' arrays (`arrays` each) together are of
-// a size that the row kernels are for (kernels_of).  In lockstep, us per step, rows / best tile sweep (with the depth
-// of one round), forward and gradient: six shots of 40 x 50 x 60 30.0 / 31.6 and 112.9 / 133.6,
-// eight of 64^3 46.7 / 50.6 and 208.7 / 212.1, four of 96 x 80 x 72 (106 MB) 54.1 / 54.3 and 244.2
-// / 244.3, four of 128 x 96 x 80 (189 MB) 71.5 / 79.7 and 342.3 / 348.2.
+// a size that the row kernels are for (kernels_of).  In lockstep, us per step, rows / fastest sweep,
+// forward and gradient: six shots of 40 x 50 x 60 28.0 / 30.8 and 111 / 127, twelve 53.2 / 52.0 and
+// 208 / 209, seven of 64^3 44.4 / 50.5 and 190 / 193, three of 100 x 90 x 70 (92 and 222 MB) 46.7 /
+// 50.7 and 220 / 212, two of 128 x 96 x 80 39.3 / 48.0 and 180 / 191, four (forward only, 189 MB)
+// 77.9 / 84.6.
 inline bool batch_rows(bool tiles_set, const fd3d_ctx *const *ctx, int ns, int arrays)
 {
     if (tiles_set) return false;
@@ -201,8 +202,8 @@ inline void make_groups(fd3d_batch *b)
     for (int s = 0; s < b->nshot; ++s) b->order[s] = s;
     BatchGroup all = whole_batch(b);
     // with neither schedule nor tile shapes selected, groups that stay in the Infinity Cache
-    // (one shot per group where a shot alone exceeds it): three shots of 128^3 118.4 us per step
-    // against 134 in lockstep, two each of 128^3, 192 x 192 x 128 and 256 x 256 x 128 584 against 752
+    // (one shot per group where a shot alone exceeds it): three shots of 128^3 112 us per step against
+    // 120 in lockstep, two each of 128^3, 192 x 192 x 128 and 256 x 256 x 128 584 against 716
     const size_t budget = b->sched_set || b->tiles_set ? b->group_bytes : (size_t)kRowBytes32;
     if (budget == 0) {
         if (batch_rows(b->tiles_set, b->ctx.data(), b->nshot, kForwardArrays)) all.rows = batch_row_maps(b);

@@ -545,10 +545,9 @@ inline bool stream_model(const fd3d_ctx *c)
     return 12.0 * (double)c->n[0] * (double)c->n[1] * (double)c->n[2] * (double)c->tsize > kInfinityCacheBytes;
 }
 
-// rec (stress passes of the forward only): the
-// step's receiver sampling, carried by the row or tile launch or launched after the cell
-// kernel.  Forward passes (velocity, stress and
-// their storing variants); defined for float and double, with and without free surface.
+// One forward pass (velocity, stress or their storing variants); defined for float and double,
+// with and without free surface.  rec (stress passes of the forward only): the step's receiver
+// sampling, carried by the row or tile launch or launched after the cell kernel.
 template <typename T, bool FS>
 void launch_pass(const fd3d_ctx *c, Kern kern, const Grid<T> &G, const Inject<T> &inj, int n, int pass, hipStream_t st,
                  const RecJob<T> &rec = RecJob<T>{});

@@ -9,7 +9,8 @@
 // range check; no load sits behind a branch, and all loads of a cell are in flight together.
 // On grids of some million cells the fabric behind the L2s bounds them: neighbouring rows and
 // planes are dealt to one XCD in an order that keeps them in its L2, and the L2s then miss the
-// compulsory bytes only (41 + 12 B per cell in the velocity pass, FP32, by the counters).
+// compulsory bytes only (42 + 12 B per cell in the velocity pass and 46 + 24 in the stress pass
+// at 128^3, FP32, by the counters, of 40 + 12 and 44 + 24).
 // Grids larger than the cache belong to the tile sweeps, whose long streams HBM serves
 // faster.  Forward step (both passes, receivers included), FP32, MI355X, us, against the best
 // tile sweep and the one-thread-per-cell kernels with a bounds test per load (vel_cell):
