@@ -161,3 +161,16 @@ def test_batch_default_groups(tune):
     batch.close()
     for s in sims:
         s.close()
+
+
+@pytest.mark.parametrize("shape", [(4, 5, 70000), (70000, 4, 5), (5, 70000, 4)])
+def test_thin_grids(shape):
+    """Rows, planes and column blocks by the ten thousand: the longest axis decides which of a
+    launch's dimensions grows (planes per slab, strips, blocks of a row)."""
+    (lam, mu, rho), shot = setup((12, 11, 10))
+    n = max(shape)
+    model = [m.mean() * (1.0 + 0.1 * np.sin(np.arange(np.prod(shape)) / 3.0).reshape(shape[::-1])) for m in (lam, mu, rho)]
+    pos = np.array([0.5 * k if k == n else 1.6 for k in shape])
+    shot["src_pos"] = tuple(pos)
+    shot["rec_pos"] = [pos + [2.2 if k == n else 0.2 for k in shape]]
+    same(both(model, torch.float32, lambda s: (s.forward(**shot), s.state())))
